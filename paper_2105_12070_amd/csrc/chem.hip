@@ -151,10 +151,9 @@ __global__ __launch_bounds__(max_threads<NP>()) void k_rhs_jac(IntArgs a, const 
   }
   wsync();
   const double y = lane < N ? st[(int64_t)lane * a.ld + c] : 0.0;
-  double row[NP];
   double fv;
   if (J) {
-    fv = jac_pass<NP>(m, w, y, a.p, lane, row);
+    fv = jac_pass<NP>(m, w, y, a.p, lane);
     if (lane < N)
       for (int j = 0; j < N; ++j) J[((size_t)c * N + lane) * N + j] = w.J[lane * m.d.S + j];
   } else {
@@ -164,50 +163,55 @@ __global__ __launch_bounds__(max_threads<NP>()) void k_rhs_jac(IntArgs a, const 
 }
 
 template <int NP>
-__global__ __launch_bounds__(256) void k_lu_solve(int64_t nmat, int n, const double* A, double* b, int32_t* info) {
-  __shared__ int slots[4][64];
+__global__ __launch_bounds__(256, 2) void k_lu_solve(int64_t nmat, int n, const double* A, double* b, int32_t* info) {
+  __shared__ double scr[4][LU_SCRATCH];
   const int wv = threadIdx.x / WAVE;
   const int64_t mi = (int64_t)blockIdx.x * (blockDim.x / WAVE) + wv;
   if (mi >= nmat) return;
   const int lane = lane_id();
+  MatTiles<NP> M;
+  load_tiles<NP>(A + (size_t)mi * n * n, n, lane, M);
   double row[NP];
-#pragma unroll
-  for (int j = 0; j < NP; ++j) row[j] = (lane < n && j < n) ? A[((size_t)mi * n + lane) * n + j] : 0.0;
-  int mystep;
-  double myrdiag;
-  const int rc = lu_factor<NP>(row, n, lane, mystep, myrdiag);
+  LuPiv<NP> lu;
+  const int rc = lu_factor<NP>(M, row, n, lane, lu, scr[wv]);
   if (lane == 0) info[mi] = rc;
   if (rc) return;
-  const int src = permute_rows<NP>(row, n, lane, mystep, myrdiag, slots[wv]);
   const double bi = lane < n ? b[(size_t)mi * n + lane] : 0.0;
-  const double x = lu_solve<NP>(row, n, lane, src, myrdiag, bi);
+  const double x = lu_solve<NP>(row, lu, bi);
   if (lane < n) b[(size_t)mi * n + lane] = x;
 }
 
 // getrf of each matrix: LU in LAPACK's layout (rows in pivot order) and ipiv.
 template <int NP>
-__global__ __launch_bounds__(256) void k_lu_factor(int64_t nmat, int n, const double* A, double* LU, int32_t* ipiv,
+__global__ __launch_bounds__(256, 2) void k_lu_factor(int64_t nmat, int n, const double* A, double* LU, int32_t* ipiv,
                                                    int32_t* info) {
-  __shared__ int slots[4][64];
+  __shared__ double scr[4][LU_SCRATCH];
   const int wv = threadIdx.x / WAVE;
   const int64_t mi = (int64_t)blockIdx.x * (blockDim.x / WAVE) + wv;
   if (mi >= nmat) return;
   const int lane = lane_id();
+  MatTiles<NP> M;
+  load_tiles<NP>(A + (size_t)mi * n * n, n, lane, M);
   double row[NP];
-#pragma unroll
-  for (int j = 0; j < NP; ++j) row[j] = (lane < n && j < n) ? A[((size_t)mi * n + lane) * n + j] : 0.0;
-  int mystep, myipiv = 0;
-  double myrdiag;
-  const int rc = lu_factor<NP>(row, n, lane, mystep, myrdiag, false, &myipiv);
+  LuPiv<NP> lu;
+  const int rc = lu_factor<NP>(M, row, n, lane, lu, scr[wv]);
   if (lane == 0) info[mi] = rc;
   if (rc) return;  // some rows never became pivots: no permutation to apply
-  permute_rows<NP>(row, n, lane, mystep, myrdiag, slots[wv]);
   if (lane < n) {
 #pragma unroll
     for (int j = 0; j < NP; ++j)
-      if (j < n) LU[((size_t)mi * n + lane) * n + j] = row[j];
-    ipiv[(size_t)mi * n + lane] = myipiv;
+      if (j < n) LU[((size_t)mi * n + lu.step) * n + j] = row[j];
   }
+  // ipiv[k]: the position of the step-k pivot row before its interchange
+  int pos = lane, my = 0;
+#pragma clang loop unroll(disable)
+  for (int k = 0; k < n; ++k) {
+    const int pj = __builtin_amdgcn_readlane(lu.src, k), pp = __builtin_amdgcn_readlane(pos, pj);
+    my = lane == k ? pp : my;
+    const int np = pos == k ? pp : pos;
+    pos = lane == pj ? k : np;
+  }
+  if (lane < n) ipiv[(size_t)mi * n + lane] = my;
 }
 
 // ---------------------------------------------------------------- workgroup path (64 < N <= 256)

@@ -61,11 +61,14 @@ struct CellWs {
   double* C;    // [64+1] concentrations, C[K] = 1 (padding species)
   double* g;    // [64+1] g/RT (reused for mass enthalpy in the Jacobian pass)
   double* hR;   // [64+1] h/RT
-  int* slot;    // [64] row permutation scratch
+  double* lu;   // [256] scratch of the LU (overlays rk .. rdm)
 };
 
 // Everything of a wave's workspace but the Jacobian block.
-__host__ __device__ inline int wave_rates_doubles(int R, int R0) { return 3 * R + (R - R0 + 1) + 3 * 66 + 32; }
+__host__ __device__ inline int wave_rates_doubles(int R, int R0) {
+  const int rates = 3 * R + (R - R0 + 1);
+  return (rates > 256 ? rates : 256) + 3 * 66;  // the LU's scratch overlays the rates
+}
 // S = NP + 1, so reads of static columns j < NP + 1 from any row stay inside
 // the J block (its last row is followed by the reaction arrays).
 __host__ __device__ inline int cell_ws_doubles(int N, int S, int R, int R0) { return N * S + wave_rates_doubles(R, R0); }
@@ -78,10 +81,10 @@ __device__ inline CellWs make_ws(double* base, const MechDims& d, bool with_J = 
   w.rkr = w.rk + d.R;
   w.rdt = w.rkr + d.R;
   w.rdm = w.rdt + d.R;
-  w.C = w.rdm + (d.R - d.R0 + 1);
+  w.lu = w.rk;
+  w.C = w.rk + (wave_rates_doubles(d.R, d.R0) - 3 * 66);
   w.g = w.C + 66;
   w.hR = w.g + 66;
-  w.slot = (int*)(w.hR + 66);
   return w;
 }
 
@@ -325,7 +328,7 @@ __device__ inline double rhs(const MechView& m, const CellWs& w, double y, doubl
 //   J_kj = (W_k/W_j) dw_k/dC_j + W_k Wbar/(rho W_j) (w_k - s_k),  s_k = sum_i C_i dw_k/dC_i
 //   J_kT = (W_k/rho) (dw_k/dT - s_k/T + w_k/T)
 //   J_Tj = -(sum_k hm_k J_kj + f_T cpm_j)/c_p,  J_TT = -(sum_k hm_k J_kT + sum_k cpm_k f_k + f_T dc_p/dT)/c_p
-// (hm, cpm: mass-specific enthalpy and heat capacity).  `row` is scratch.
+// (hm, cpm: mass-specific enthalpy and heat capacity).
 // One-sided finite-difference Jacobian (the ablation of section 2.3): column
 // j is (f(y + d_j e_j) - f(y)) / d_j with d_j = sqrt(eps) max(|y_j|, 1e-10)
 // rounded to a representable step; N + 1 evaluations of f.  Returns f(y).
@@ -340,13 +343,15 @@ __device__ inline double jac_fd(const MechView& m, const CellWs& w, double y, do
     const double fj = rhs(m, w, lane == j ? yj + d : y, p, lane);
     if (lane < N) w.J[lane * S + j] = (fj - f0) / d;
   }
+  if (lane < N)
+    for (int j = N; j < S; ++j) w.J[lane * S + j] = 0.0;  // padding columns
   wsync();
   return f0;
 }
 
 template <int NP, bool PROF = false>
 __device__ inline double jac_pass(const MechView& m, const CellWs& w, double y, double p, int lane,
-                                  double (&row)[NP], Prof<PROF>* pf = nullptr, bool fd = false) {
+                                  Prof<PROF>* pf = nullptr, bool fd = false) {
   if (PROF && fd) return jac_fd(m, w, y, p, lane);
   const int K = m.d.K, R = m.d.R, N = m.d.N, S = m.d.S;
   const unsigned long long t0 = PROF ? pf->now() : 0ull;
@@ -503,187 +508,323 @@ __device__ __forceinline__ double recip(double x) {
   return fma(r, e, r);
 }
 
-// LU with partial pivoting of the row-per-lane matrix, with getrf's pivot
-// rule: at step k the pivot is the unpivoted row of largest |a|, exact ties
-// going to the row that comes first in getrf's current row order (the order
-// after the interchanges k <-> pivot of the earlier steps).  No rows move: the
-// lane chosen at step k records mystep = k, and pos tracks where getrf would
-// hold the lane's row.  L multipliers of step k stay in column k of the
-// remaining rows.  |a| is compared as an integer key: the upper 32 bits
-// (sign cleared) by one wave max; only when several lanes share the largest
-// upper half do the lower halves, and then the positions, decide.
-// Steps run in static phases of four: phase P only touches columns >= 4P.
-// Inside a phase the four columns of chunk P rotate through c0..c3 so that
-// the pivot column is always c0; every register index is static.
-// Returns the 1-based step of a zero pivot, or 0.  myipiv (lane k) receives
-// getrf's ipiv[k]: the position the step-k pivot row held before its interchange.
+// What a factorisation leaves besides the factors in the row registers.  Rows
+// stay in their lanes: the row chosen at step k is lane piv(k)'s, its L part in
+// columns < k and its U part in columns >= k.  Padding rows (lane >= N) count as
+// chosen at their own step.
 template <int NP>
-__device__ inline int lu_factor(double (&row)[NP], int N, int lane, int& mystep, double& myrdiag,
-                                bool nopiv = false, int* myipiv = nullptr) {
-  mystep = lane < N ? -1 : (1 << 20);
-  myrdiag = 0.0;
-  int info = 0;
+struct LuPiv {
+  unsigned pk[NP / 4];  // piv(4P) .. piv(4P + 3), one per byte (wave-uniform)
+  int step;             // the step at which this lane's row was the pivot
+  int src;              // piv(lane)
+  double rdiag;         // 1 / U_kk of this lane's row
+  __device__ __forceinline__ int piv(int k) const { return (int)((pk[k / 4] >> (8 * (k % 4))) & 63u); }
+};
+
+// Where getrf holds this lane's row before step k: the interchanges
+// j <-> position of piv(j) of the earlier steps, replayed (src: lane j < k holds piv(j)).
+__device__ inline int getrf_pos(int src, int k, int lane) {
   int pos = lane;
-#pragma clang loop unroll(full)
-  for (int P = 0; P < NP / 4; ++P) {
-    const int k0 = 4 * P;
-    const int k1 = min(k0 + 4, N);
-    double c0 = row[k0], c1 = row[k0 + 1], c2 = row[k0 + 2], c3 = row[k0 + 3];
 #pragma clang loop unroll(disable)
-    for (int k = k0; k < k1; ++k) {
-      const int kk = k - k0;
-      const bool elig = mystep < 0;
-      const unsigned long long mag = __builtin_bit_cast(unsigned long long, c0) & 0x7fffffffffffffffull;
-      const unsigned key = elig ? (unsigned)(mag >> 32) : 0u;
-      const unsigned kmax = wave_max_u32(key);
-      unsigned long long cand = ballot(elig && key == kmax);
-      bool sing = kmax == 0u;
-      if (!nopiv && (sing || (cand & (cand - 1)) != 0ull)) {  // wave-uniform: rare tie path
-        const bool c = elig && key == kmax;
-        const unsigned lmax = wave_max_u32(c ? (unsigned)mag : 0u);
-        sing = sing && lmax == 0u;
-        cand = ballot(c && (unsigned)mag == lmax);
-        if ((cand & (cand - 1)) != 0ull) {
-          const bool tie = ((cand >> lane) & 1ull) != 0ull;
-          const int pmin = 63 - (int)wave_max_u32(tie ? (unsigned)(63 - pos) : 0u);
-          cand = ballot(tie && pos == pmin);
-        }
-      }
-      // a zero pivot column is recorded and the factorisation runs on with
-      // zero multipliers (no early exit keeps the control flow simple)
-      // without pivoting (ablation) the pivot is row k itself
-      if (nopiv) sing = !(readlane(c0, k) != 0.0);
-      if (sing && info == 0) info = k + 1;
-      const int p = sing ? 0 : (nopiv ? k : uniform_int(__builtin_ctzll(cand)));
-      {  // getrf interchanges rows k and pos(p)
-        const int pp = sing ? k : uniform_int(__builtin_amdgcn_readlane(pos, p));
-        if (myipiv && lane == k) *myipiv = pp;
-        const int np = pos == k ? pp : pos;
-        pos = (lane == p && !sing) ? k : np;
-      }
-      const double piv = readlane(c0, p);
-      const double rp = recip(piv);
-      const bool upd = elig && lane != p && !sing;
-      if (lane == p && !sing) {
-        mystep = k;
-        myrdiag = rp;
-      }
-      const double l = upd ? c0 * rp : 0.0;
-      // c1..c3 hold columns k+1.. of the chunk first, then finished columns
-      double u1 = readlane(c1, p), u2 = readlane(c2, p), u3 = readlane(c3, p);
-      u1 = kk <= 2 ? u1 : 0.0;
-      u2 = kk <= 1 ? u2 : 0.0;
-      u3 = kk == 0 ? u3 : 0.0;
-      c1 = fma(-l, u1, c1);
-      c2 = fma(-l, u2, c2);
-      c3 = fma(-l, u3, c3);
-      c0 = upd ? l : c0;
-      // four broadcasts in flight before their four FMAs: the scalar
-      // registers differ, so no broadcast waits on the previous FMA
-#pragma unroll
-      for (int j = k0 + 4; j < NP; j += 4) {
-        const double u0 = readlane(row[j], p), v1 = readlane(row[j + 1], p);
-        const double v2 = readlane(row[j + 2], p), v3 = readlane(row[j + 3], p);
-        __builtin_amdgcn_sched_barrier(0);
-        row[j] = fma(-l, u0, row[j]);
-        row[j + 1] = fma(-l, v1, row[j + 1]);
-        row[j + 2] = fma(-l, v2, row[j + 2]);
-        row[j + 3] = fma(-l, v3, row[j + 3]);
-      }
-      const double t = c0;
-      c0 = c1;
-      c1 = c2;
-      c2 = c3;
-      c3 = t;
-    }
-    // a short final phase re-aligns the rotation
-#pragma clang loop unroll(disable)
-    for (int r = max(k1 - k0, 0); r < 4; ++r) {
-      const double t = c0;
-      c0 = c1;
-      c1 = c2;
-      c2 = c3;
-      c3 = t;
-    }
-    row[k0] = c0;
-    row[k0 + 1] = c1;
-    row[k0 + 2] = c2;
-    row[k0 + 3] = c3;
+  for (int j = 0; j < k; ++j) {
+    const int pj = __builtin_amdgcn_readlane(src, j), pp = __builtin_amdgcn_readlane(pos, pj);
+    const int np = pos == j ? pp : pos;
+    pos = lane == pj ? j : np;
   }
+  return pos;
+}
+
+// The rare outcome of a pivot search: the lanes of cand share the largest upper
+// half kmax of |a|.  The largest lower half decides, then getrf's row order.
+// Returns a mask whose lowest lane is the pivot; records a zero pivot.  With no
+// row left (a padding step) the pivot is lane k.
+__device__ inline unsigned long long lu_tie(unsigned long long cand, unsigned kmax, unsigned lo, int src, int k,
+                                            int lane, int& info) {
+  if (!cand) return 1ull << k;
+  unsigned best = 0;
+  unsigned long long top = 0;
+#pragma clang loop unroll(disable)
+  for (; cand; cand &= cand - 1) {
+    const unsigned v = (unsigned)__builtin_amdgcn_readlane((int)lo, __builtin_ctzll(cand));
+    const unsigned long long bit = cand & (0ull - cand);
+    top = v > best ? bit : (v == best ? top | bit : top);
+    best = v > best ? v : best;
+  }
+  if ((kmax | best) == 0u && info == 0) info = k + 1;
+  if ((top & (top - 1)) == 0ull) return top;
+  const int pos = getrf_pos(src, k, lane);
+  int pmin = 64;
+  unsigned long long first = 0;
+#pragma clang loop unroll(disable)
+  for (; top; top &= top - 1) {
+    const int v = __builtin_amdgcn_readlane(pos, __builtin_ctzll(top));
+    first = v < pmin ? top & (0ull - top) : first;
+    pmin = v < pmin ? v : pmin;
+  }
+  return first;
+}
+
+// Doubles of the LDS scratch that lu_factor uses (four rows of U).
+constexpr int LU_SCRATCH = 4 * WAVE;
+
+// The matrix as the factorisation takes it: 16 x 16 tiles of the transposed
+// matrix, x[t][g] of lane l = element (row 16 t + l % 16, column 4 g + l / 16).
+template <int NP>
+struct MatTiles {
+  static constexpr int NT = (NP + 15) / 16;
+  double x[4][4 * NT];
+};
+
+// LU with partial pivoting, with getrf's pivot rule: at step k the pivot is the
+// unpivoted row of largest |a|, exact ties going to the row that comes first in
+// getrf's current row order.  No rows move; the factors come out row-per-lane.
+// |a| is compared as an integer key: the upper 32 bits (sign cleared) by one
+// wave max; only when several lanes share the largest upper half do the lower
+// halves, and then the positions, decide.  Returns the 1-based step of the
+// first zero pivot (the factors are then meaningless), or 0.
+//
+// Bound: VALU issue and, with few waves, the chain of pivot searches.  In
+// row-per-lane form every column right of the pivot costs two readlanes and an
+// FMA at every step, about 22 issue cycles, most of them spent on the
+// broadcast.  So the columns are taken four at a time, and the rest of the
+// matrix gets one rank-4 update per panel on the FP64 matrix cores
+// (v_mfma_f64_16x16x4, 64 cycles for 1,024 FMAs: the FMA rate without the
+// broadcasts).  In the tile layout the four columns of a panel are one register
+// per row tile: a block_transpose turns them into row-per-lane columns for the
+// pivot search, and the multipliers come out of a second one in the
+// instruction's operand layout.  The instruction adds its four products in
+// order with one rounding each, and a rank-4 update is four steps of the
+// elimination, so the factors are those of the step-by-step elimination bit
+// for bit.  The panel's pivot rows go through LDS (lane = column) for the 4 x 4
+// triangular solve.  Within a column tile the four panels share one loop body:
+// the tile's registers rotate by one column group per panel, so the current
+// group is always the first (unrolled over all panels the code, 110 KB for the
+// integrator, no longer fits the instruction cache).
+// Measured for N = 55 (shader cycles of one factorisation, two waves per SIMD /
+// one wave): 87.9k / 67.5k row-per-lane with the rows permuted at the end, 54.7k /
+// 42.3k this way (a solve with the factors 5.7k / 5.2k -> 2.9k / 2.2k).
+template <int NP>
+__device__ __forceinline__ int lu_factor(MatTiles<NP>& M, double (&row)[NP], int N, int lane, LuPiv<NP>& f, double* ub,
+                                         bool nopiv = false) {
+  constexpr int NG = NP / 4, NT = MatTiles<NP>::NT;  // column groups; row and column tiles
+  f.step = lane;
+  f.src = lane;
+  f.rdiag = 0.0;
+  int info = 0;
+  bool elig = lane < N;
+  int packed = 0x03020100 + 0x04040404 * lane;  // lane g: piv(4 g) .. piv(4 g + 3)
+  auto& X = M.x;
+  const int n16 = lane & 15, cb = lane >> 4;
+  static_for<0, NT>([&](auto Tcc) __attribute__((always_inline)) {
+    constexpr int tc = decltype(Tcc)::value, g0 = 4 * tc;
+    // column that this lane reads of the pivot rows; the lanes of the current
+    // tile follow its rotation
+    int ucol = lane;
+#pragma clang loop unroll(disable)
+    for (int v = 0; v < 4; ++v) {
+      const int k0 = 16 * tc + 4 * v;
+      // X[t][g0 + j]: column group g0 + (v + j) % 4; groups before v hold the
+      // finished columns row-per-lane (X[q] = column 4 g + q)
+      double c[4] = {X[0][g0], X[1][g0], X[2][g0], X[3][g0]};
+      double nl[4] = {0.0, 0.0, 0.0, 0.0};  // minus the multipliers, 0 in the rows already chosen
+      int p[4] = {k0, k0 + 1, k0 + 2, k0 + 3};
+      const unsigned long long open = ballot(elig);  // rows not chosen before this panel
+      if (k0 < N) {
+        block_transpose(c);
+        static_for<0, 4>([&](auto Qc) __attribute__((always_inline)) {
+          constexpr int q = decltype(Qc)::value;
+          const int k = k0 + q;
+          // every lane's reciprocal is formed while the search runs (the asm keeps
+          // it before the branch)
+          double r = recip(c[q]);
+          const unsigned hi = (unsigned)(__builtin_bit_cast(unsigned long long, c[q]) >> 32) & 0x7fffffffu;
+          const unsigned key = elig ? hi : 0u;
+          const unsigned kmax = wave_max_u32(key);
+          unsigned long long cand = ballot(key == kmax);
+          asm volatile("" : "+v"(r));
+          // one lane, unless several share the upper half or every key is 0
+          if (__builtin_expect(__builtin_popcountll(cand) != 1, 0)) {
+            const unsigned lo = (unsigned)__builtin_bit_cast(unsigned long long, c[q]);
+            cand = lu_tie(ballot(elig) & cand, kmax, lo, f.src, k, lane, info);
+          }
+          int pq = uniform_int(__builtin_ctzll(cand));
+          if (nopiv && k < N) {  // ablation: the pivot is row k itself
+            pq = k;
+            if (!(readlane(c[q], k) != 0.0) && info == 0) info = k + 1;
+          }
+          p[q] = pq;
+          const bool me = lane == pq;
+          const double rp = readlane(r, pq);
+          f.src = writelane(pq, k, f.src);
+          f.step = writelane(k, pq, f.step);
+          f.rdiag = me ? r : f.rdiag;
+          elig = elig && !me;
+          const double nlq = -(c[q] * rp);
+          nl[q] = elig ? nlq : 0.0;
+          c[q] = elig ? -nlq : c[q];
+#pragma unroll
+          for (int j = q + 1; j < 4; ++j) c[j] = fma(nl[q], readlane(c[j], pq), c[j]);
+        });
+        packed = writelane(p[0] | (p[1] << 8) | (p[2] << 16) | (p[3] << 24), g0 + v, packed);
+      }
+      // the tile's groups move up by one; the finished one goes last
+      static_for<0, 4>([&](auto Tc) __attribute__((always_inline)) {
+        constexpr int t = decltype(Tc)::value;
+        X[t][g0] = X[t][g0 + 1];
+        X[t][g0 + 1] = X[t][g0 + 2];
+        X[t][g0 + 2] = X[t][g0 + 3];
+        X[t][g0 + 3] = c[t];
+      });
+      ucol = (lane >> 4) == tc ? (ucol & ~12) | ((ucol + 4) & 12) : lane;
+      if (k0 + 4 < N) {
+        // the panel's pivot rows, open columns, to LDS: ub[q][column]
+        wsync();
+        const unsigned tiles = (1u << (p[0] >> 4)) | (1u << (p[1] >> 4)) | (1u << (p[2] >> 4)) | (1u << (p[3] >> 4));
+        auto put = [&](auto Tc) __attribute__((always_inline)) {
+          constexpr int t = decltype(Tc)::value;
+          const int r = 16 * t + n16;
+          int q = r == p[0] ? 0 : -1;
+          q = r == p[1] ? 1 : q;
+          q = r == p[2] ? 2 : q;
+          q = r == p[3] ? 3 : q;
+          asm("" : "+v"(q));  // one compare, not four branches
+          if (q >= 0) {
+            double* d = ub + q * WAVE + cb;
+            d[16 * tc + ((4 * v + 4) & 15)] = X[t][g0];
+            d[16 * tc + ((4 * v + 8) & 15)] = X[t][g0 + 1];
+            d[16 * tc + ((4 * v + 12) & 15)] = X[t][g0 + 2];
+            static_for<g0 + 4, NG>([&](auto Hc) __attribute__((always_inline)) {
+              constexpr int h = decltype(Hc)::value;
+              d[4 * h] = X[t][h];
+            });
+          }
+        };
+        if (__builtin_expect((tiles & (1u << tc)) != 0u, 1)) put(Tcc);
+        if (__builtin_expect((tiles & ~(1u << tc)) != 0u, 0)) {  // usually all four are rows of the diagonal tile
+          static_for<0, NT>([&](auto Tc) __attribute__((always_inline)) {
+            constexpr int t = decltype(Tc)::value;
+            if constexpr (t != tc)
+              if ((tiles >> t) & 1u) put(Tc);
+          });
+        }
+        // 0 in the tile's finished columns, whose registers the update then leaves alone
+        if (n16 < 4 * v + 4) ub[cb * WAVE + 16 * tc + n16] = 0.0;
+        wsync();
+        // lane = column: rows k0 .. k0 + 3 of U by forward substitution (columns
+        // left of the tile are not used, nor are those past the last group)
+        double u[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) u[q] = ub[q * WAVE + ucol];
+#pragma unroll
+        for (int q = 1; q < 4; ++q)
+#pragma unroll
+          for (int j = 0; j < q; ++j) u[q] = fma(readlane(nl[j], p[q]), u[j], u[q]);
+        block_transpose(u);   // -> operand A of column tile c, lane i: U[k0 + i / 16][16 c + i % 16]
+        block_transpose(nl);  // -> operand B of row tile t, lane i: -L[16 t + i % 16][k0 + i / 16]
+        // The lane swaps write both operands, and the compiler (ROCm 7.2) does not
+        // keep the wait states that an MFMA reading the second one needs: one
+        // instruction after the swap it read the old value.
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_nop 3");
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<0, NT>([&](auto Tc) __attribute__((always_inline)) {
+          constexpr int t = decltype(Tc)::value;
+          // a tile above the diagonal one has usually no open row left
+          if (t >= tc || __builtin_expect(((open >> (16 * t)) & 0xffffull) != 0ull, 0)) {
+            static_for<tc, NT>([&](auto Cc) __attribute__((always_inline)) {
+              constexpr int ct = decltype(Cc)::value;
+              dbl4 d = {X[t][4 * ct], X[t][4 * ct + 1], X[t][4 * ct + 2], X[t][4 * ct + 3]};
+              d = __builtin_amdgcn_mfma_f64_16x16x4f64(u[ct], nl[t], d, 0, 0, 0);
+              X[t][4 * ct] = d[0], X[t][4 * ct + 1] = d[1], X[t][4 * ct + 2] = d[2], X[t][4 * ct + 3] = d[3];
+            });
+          }
+        });
+      }
+    }
+  });
+  if (lane >= N) f.rdiag = 0.0;
+  static_for<0, NG>([&](auto Gc) __attribute__((always_inline)) {
+    constexpr int g = decltype(Gc)::value;
+    f.pk[g] = (unsigned)__builtin_amdgcn_readlane(packed, g);
+    row[4 * g] = X[0][g], row[4 * g + 1] = X[1][g], row[4 * g + 2] = X[2][g], row[4 * g + 3] = X[3][g];
+  });
   return info;
 }
 
-// Moves the factored rows into pivot order (lane k receives the row chosen
-// at step k), so that L is unit lower and U upper with lane = row; src is the
-// lane each lane took its row from.
+// Solve M x = b with the factors as lu_factor leaves them; lane i holds b_i
+// and gets x_i.  Forward substitution with the unit-lower L and back
+// substitution with U, both by columns: the value of step k is broadcast from
+// lane piv(k) and every lane applies the column's update (a lane past its own
+// step only changes a value that has already been read), so no per-element
+// triangle mask is formed.  y_k is kept in its row's lane, x_k goes to lane k.
 template <int NP>
-__device__ inline int permute_rows(double (&row)[NP], int N, int lane, int mystep, double& myrdiag, int* slot) {
-  if (lane < N) slot[mystep] = lane;
-  wsync();
-  const int src = lane < N ? slot[lane] : lane;
-  wsync();
-#pragma unroll
-  for (int j = 0; j < NP; ++j) row[j] = __shfl(row[j], src);
-  myrdiag = __shfl(myrdiag, src);
-  return src;
-}
-
-// Solve M x = b with the permuted factors; lane i holds b_i and gets x_i.
-// The right-hand side is gathered into pivot order, then forward substitution
-// with the unit-lower L and back substitution with U (both by columns, the
-// value of step k broadcast from lane k).  Every lane applies every column's
-// update (a lane past its own step only changes a value it has already
-// saved), so no per-element triangle mask is formed: masks of the factors
-// would be loop invariants across a step's four solves and would hold two
-// masked copies of the row in registers.
-template <int NP>
-__device__ inline double lu_solve(const double (&row)[NP], int N, int lane, int src, double myrdiag, double b) {
-  // padding lanes carry b = 0 and zero rows, so all NP steps run unconditionally
-  (void)N;
-  b = __shfl(b, src);
+__device__ inline double lu_solve(const double (&row)[NP], const LuPiv<NP>& f, double b) {
+  // padding rows carry b = 0 and zeros, so all NP steps run unconditionally
   double y = 0.0;
 #pragma unroll
   for (int k = 0; k < NP; ++k) {
-    const double yk = readlane(b, k);
-    y = lane == k ? b : y;  // lane k's value is final at step k
+    const int pk = f.piv(k);
+    const double yk = readlane(b, pk);
+    y = writelane(yk, pk, y);
     b = fma(-row[k], yk, b);
   }
   b = y;
   double x = 0.0;
 #pragma unroll
   for (int k = NP - 1; k >= 0; --k) {
-    const double bk = b * myrdiag;
-    const double xk = readlane(bk, k);
-    x = lane == k ? bk : x;
+    const double xk = readlane(b * f.rdiag, f.piv(k));
+    x = writelane(xk, k, x);
     b = fma(-row[k], xk, b);
   }
   return x;
 }
 
-// M = I/(gamma h) - J from the LDS Jacobian into row registers.  Returns
-// false if a row holds a non-finite value.
+// M = I/(gamma h) - J from the LDS Jacobian into tiles.  Returns false if an
+// entry is not finite.
 template <int NP>
-__device__ inline bool form_matrix(const CellWs& w, int N, int S, int lane, double d, double (&row)[NP]) {
-  double chk = 0.0;
-#pragma unroll
-  for (int j = 0; j < NP; ++j) row[j] = 0.0;
+__device__ inline bool form_matrix(const CellWs& w, int N, int S, int lane, double d, MatTiles<NP>& M) {
+  constexpr int NG = NP / 4, NT = MatTiles<NP>::NT;
+  constexpr int NMIN = NP == 16 ? 1 : NP == 32 ? 17 : NP == 56 ? 33 : 57;  // smallest N this NP serves
+  double chk = 0.0, jd = 0.0;
   if (lane < N) {
-    double* Jr = w.J + lane * S;
-    const double jd = Jr[lane];
-    Jr[lane] = jd - d;
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    // every load is in the row (j < NP < S) and taken unconditionally; the
-    // padding columns are selected away, so the unrolled loop has no branches
-#pragma unroll
-    for (int j = 0; j < NP; ++j) {
-      const double v = Jr[j];
-      row[j] = j < N ? -v : 0.0;
-      chk += row[j];
-    }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    Jr[lane] = jd;
+    jd = w.J[lane * S + lane];
+    w.J[lane * S + lane] = jd - d;
   }
+  wsync();
+  static_for<0, 4>([&](auto Tc) __attribute__((always_inline)) {
+    constexpr int t = decltype(Tc)::value;
+    const int r = 16 * t + (lane & 15);
+    static_for<0, 4 * NT>([&](auto Gc) __attribute__((always_inline)) { M.x[t][decltype(Gc)::value] = 0.0; });
+    if constexpr (t < NT) {
+      if (16 * t + 15 < NMIN || r < N) {
+        // the Jacobian pass leaves zeros in the padding columns j < NP < S
+        const double* Jr = w.J + r * S + (lane >> 4);
+        static_for<0, NG>([&](auto Gc) __attribute__((always_inline)) {
+          constexpr int g = decltype(Gc)::value;
+          M.x[t][g] = -Jr[4 * g];
+          chk += M.x[t][g];
+        });
+      }
+    }
+  });
+  wsync();
+  if (lane < N) w.J[lane * S + lane] = jd;
   return ballot(!__builtin_isfinite(chk)) == 0ull;
+}
+
+// A row-major n x n matrix in global memory into tiles (zeros in the padding).
+template <int NP>
+__device__ inline void load_tiles(const double* A, int n, int lane, MatTiles<NP>& M) {
+  constexpr int NG = NP / 4, NT = MatTiles<NP>::NT;
+  const int cb = lane >> 4;
+  static_for<0, 4>([&](auto Tc) __attribute__((always_inline)) {
+    constexpr int t = decltype(Tc)::value;
+    const int r = 16 * t + (lane & 15);
+    static_for<0, 4 * NT>([&](auto Gc) __attribute__((always_inline)) {
+      constexpr int g = decltype(Gc)::value;
+      M.x[t][g] = t < NT && g < NG && r < n && 4 * g + cb < n ? A[(size_t)r * n + 4 * g + cb] : 0.0;
+    });
+  });
 }
 
 // One Rosenbrock attempt from y with f0 = f(y) and J(y) in LDS.  Writes ynew
@@ -692,26 +833,22 @@ __device__ inline bool form_matrix(const CellWs& w, int N, int S, int lane, doub
 // K0 = K_i, K1 = K_{i-1}, ..., so coefficient a_ij multiplies K_{i-1-j}.
 template <int NP, bool PROF>
 __device__ inline int ros_attempt(const MechView& m, const CellWs& w, const RosTable& tab, double p, int lane,
-                                  double y, double f0, double h, double (&row)[NP], double& ynew, double& err,
-                                  int& mystep, double& myrdiag, Prof<PROF>& pf, double* kst = nullptr,
-                                  int* srcout = nullptr, bool nopiv = false, int formed = -1) {
+                                  double y, double f0, double h, MatTiles<NP>& M, double (&row)[NP], double& ynew,
+                                  double& err, LuPiv<NP>& lu, Prof<PROF>& pf, double* kst = nullptr, bool nopiv = false,
+                                  int formed = -1) {
   const int N = m.d.N;
-  // formed: -1 form M here from the LDS Jacobian; 1 / 0: M is already in row
+  // formed: -1 form M here from the LDS Jacobian; 1 / 0: M is already there
   // (formed by the caller while it held the Jacobian), finite / not finite
   bool okm = formed == 1;
   if (formed < 0) {
     pf.start();
-    okm = form_matrix<NP>(w, N, m.d.S, lane, 1.0 / (tab.gamma * h), row);
+    okm = form_matrix<NP>(w, N, m.d.S, lane, 1.0 / (tab.gamma * h), M);
     pf.stop(1);
   }
   if (!okm) return 2;
-  const int info = lu_factor<NP>(row, N, lane, mystep, myrdiag, PROF && nopiv);
-  if (info) {
-    pf.stop(2);
-    return 1;
-  }
-  const int src = permute_rows<NP>(row, N, lane, mystep, myrdiag, w.slot);
+  const int info = lu_factor<NP>(M, row, N, lane, lu, w.lu, PROF && nopiv);
   pf.stop(2);
+  if (info) return 1;
   const double ih = 1.0 / h;
   const int s = tab.s;
   double K0 = 0.0, K1 = 0.0, K2 = 0.0, K3 = 0.0;
@@ -730,7 +867,7 @@ __device__ inline int ros_attempt(const MechView& m, const CellWs& w, const RosT
     }
     const double r = fi + ih * (c0 * K0 + c1 * K1 + c2 * K2);
     pf.start();
-    const double ki = lu_solve<NP>(row, N, lane, src, myrdiag, lane < N ? r : 0.0);
+    const double ki = lu_solve<NP>(row, lu, lane < N ? r : 0.0);
     pf.stop(4);
     K3 = K2;
     K2 = K1;
@@ -742,7 +879,6 @@ __device__ inline int ros_attempt(const MechView& m, const CellWs& w, const RosT
     kst[1] = K2;
     kst[2] = K1;
     kst[3] = K0;
-    *srcout = src;
   }
   // after s stages K0 = K_{s-1}, K1 = K_{s-2}, ...
   const double m0 = tab.m[s - 1], e0 = tab.e[s - 1];
@@ -765,7 +901,7 @@ __device__ inline int ros_attempt(const MechView& m, const CellWs& w, const RosT
 // the Jacobian pass; the values are the same bits as the first time, so the
 // results equal those of a wave that keeps its Jacobian.
 template <int NP, bool PROF>
-__device__ void integrate_cell(const MechView& m, const CellWs& w0, const IntArgs& a, int64_t c,
+__device__ __forceinline__ void integrate_cell(const MechView& m, const CellWs& w0, const IntArgs& a, int64_t c,
                                const SlotPool* pool = nullptr) {
   const int lane = lane_id();
   Prof<PROF> pf;
@@ -789,16 +925,16 @@ __device__ void integrate_cell(const MechView& m, const CellWs& w0, const IntArg
   bool rej_last = false;
   const int nck = a.tape_y ? a.max_tape / a.ckpt + 1 : 0;
   if (a.tape_y && lane < N) a.tape_y[(c * (int64_t)nck) * N + lane] = y;
+  MatTiles<NP> M;
   double row[NP];
-  int mystep;
-  double myrdiag;
+  LuPiv<NP> lu;
   int ntape = 0;
   const RosTable& tab = kTables[a.method];
   while (status == ST_OK && t < dt) {
     double f0 = 0.0;
     if (!pool) {
       pf.start();
-      f0 = jac_pass<NP, PROF>(m, w, y, a.p, lane, row, &pf, PROF && a.jac_fd);
+      f0 = jac_pass<NP, PROF>(m, w, y, a.p, lane, &pf, PROF && a.jac_fd);
       pf.stop(0);
     }
     bool fresh = true;
@@ -817,17 +953,17 @@ __device__ void integrate_cell(const MechView& m, const CellWs& w0, const IntArg
         if (sl < 0) { status = ST_NONFINITE; break; }  // unreachable unless a slot is never returned
         w.J = pool->slot(sl);
         pf.start();
-        f0 = jac_pass<NP, PROF>(m, w, y, a.p, lane, row, &pf, PROF && a.jac_fd);
+        f0 = jac_pass<NP, PROF>(m, w, y, a.p, lane, &pf, PROF && a.jac_fd);
         pf.stop(0);
-        formed = form_matrix<NP>(w, N, m.d.S, lane, 1.0 / (tab.gamma * h), row) ? 1 : 0;
+        formed = form_matrix<NP>(w, N, m.d.S, lane, 1.0 / (tab.gamma * h), M) ? 1 : 0;
         pf.stop(1);
         pool->release(sl);
         w.J = nullptr;
       }
       if (fresh && ballot(lane < N && !__builtin_isfinite(f0))) { status = ST_NONFINITE; break; }
       double ynew, err;
-      int rc = ros_attempt<NP, PROF>(m, w, tab, a.p, lane, y, f0, h, row, ynew, err, mystep, myrdiag, pf, nullptr,
-                                     nullptr, PROF && a.lu_nopiv, formed);
+      int rc = ros_attempt<NP, PROF>(m, w, tab, a.p, lane, y, f0, h, M, row, ynew, err, lu, pf, nullptr,
+                                     PROF && a.lu_nopiv, formed);
       if (rc == 0 && c >= a.fail_lu_lo && c < a.fail_lu_hi) rc = 1;  // testing: as if M were singular
       if (rc == 2 && fresh) { status = ST_NONFINITE; break; }
       fresh = false;

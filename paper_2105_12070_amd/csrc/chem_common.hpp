@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace chem {
 
 constexpr double RU = 8.314462618e7;  // gas constant, erg/(mol K)
@@ -116,7 +118,7 @@ __device__ __forceinline__ int uniform_int(int x) { return __builtin_amdgcn_read
 
 __device__ __forceinline__ double uniform_double(double x) { return readlane(x, 0); }
 
-__device__ __forceinline__ unsigned long long ballot(bool p) { return __ballot(p); }
+__device__ __forceinline__ unsigned long long ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 
 template <unsigned CTRL>
 __device__ __forceinline__ unsigned dpp(unsigned x) {
@@ -148,11 +150,58 @@ __device__ __forceinline__ unsigned wave_max_u32(unsigned x) {
   x = max(x, dpp<DPP_QP2301>(x));
   x = max(x, dpp<DPP_HMIRROR>(x));
   x = max(x, dpp<DPP_MIRROR>(x));
-  const unsigned r0 = (unsigned)__builtin_amdgcn_readlane((int)x, 0);
-  const unsigned r1 = (unsigned)__builtin_amdgcn_readlane((int)x, 16);
-  const unsigned r2 = (unsigned)__builtin_amdgcn_readlane((int)x, 32);
-  const unsigned r3 = (unsigned)__builtin_amdgcn_readlane((int)x, 48);
-  return max(max(r0, r1), max(r2, r3));
+  // lane 15 of each row into the next row (rows 1 and 3), then lane 31 into the
+  // upper half: lane 63 has the maximum (0, the identity, where nothing moves)
+  x = max(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false));
+  x = max(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false));
+  return (unsigned)__builtin_amdgcn_readlane((int)x, 63);
+}
+
+// v[q] of lane block t (lanes 16 t .. 16 t + 15) <-> v[t] of lane block q: a 4 x 4
+// transpose between the lane blocks and the registers, eight lane-swap
+// instructions.  It is its own inverse.
+typedef double dbl4 __attribute__((ext_vector_type(4)));
+template <bool SWAP32>
+__device__ __forceinline__ void lane_swap(double& a, double& b) {
+  const unsigned long long x = __builtin_bit_cast(unsigned long long, a), y = __builtin_bit_cast(unsigned long long, b);
+  unsigned lo[2], hi[2];
+  if constexpr (SWAP32) {  // upper half of a <-> lower half of b
+    const auto l = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)y, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+    lo[0] = l[0], lo[1] = l[1], hi[0] = h[0], hi[1] = h[1];
+  } else {  // odd blocks of a <-> even blocks of b
+    const auto l = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)y, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+    lo[0] = l[0], lo[1] = l[1], hi[0] = h[0], hi[1] = h[1];
+  }
+  a = __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]);
+  b = __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
+}
+__device__ __forceinline__ void block_transpose(double (&v)[4]) {
+  lane_swap<false>(v[0], v[1]);
+  lane_swap<false>(v[2], v[3]);
+  lane_swap<true>(v[0], v[2]);
+  lane_swap<true>(v[1], v[3]);
+}
+
+// x with lane l's value replaced by the wave-uniform v (l uniform): v_writelane_b32,
+// which has no clang builtin.
+__device__ int amdgcn_writelane(int v, int l, int x) __asm("llvm.amdgcn.writelane.i32");
+__device__ __forceinline__ int writelane(int v, int l, int x) { return amdgcn_writelane(v, l, x); }
+__device__ __forceinline__ double writelane(double v, int l, double x) {
+  const unsigned long long u = __builtin_bit_cast(unsigned long long, v), w = __builtin_bit_cast(unsigned long long, x);
+  const unsigned lo = (unsigned)amdgcn_writelane((int)(unsigned)u, l, (int)(unsigned)w);
+  const unsigned hi = (unsigned)amdgcn_writelane((int)(unsigned)(u >> 32), l, (int)(unsigned)(w >> 32));
+  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+
+// f(integral_constant I), I = B .. E - 1, in straight-line code.
+template <int B, int E, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (B < E) {
+    f(std::integral_constant<int, B>());
+    static_for<B + 1, E>(f);
+  }
 }
 
 // Orders the wave's LDS traffic between phases in which lanes read what

@@ -28,7 +28,7 @@ __device__ __forceinline__ double sx_pick(const double (&r)[SX_KMAX], int i) {
 }
 
 template <int NP, bool PROF>
-__device__ void integrate_cell_sx(const MechView& m, const CellWs& w, const IntArgs& a, int64_t c) {
+__device__ __forceinline__ void integrate_cell_sx(const MechView& m, const CellWs& w, const IntArgs& a, int64_t c) {
   const int lane = lane_id();
   const int N = m.d.N;
   Prof<PROF> pf;
@@ -50,12 +50,12 @@ __device__ void integrate_cell_sx(const MechView& m, const CellWs& w, const IntA
   double t = 0.0;
   bool rej_last = false;
   int k = 3;
+  MatTiles<NP> M;
   double row[NP];
-  int mystep;
-  double myrdiag;
+  LuPiv<NP> lu;
   while (status == ST_OK && t < dt) {
     pf.start();
-    const double f0 = jac_pass<NP, PROF>(m, w, y, a.p, lane, row, &pf);
+    const double f0 = jac_pass<NP, PROF>(m, w, y, a.p, lane, &pf);
     pf.stop(0);
     bool fresh = true;
     int nsing = 0;
@@ -78,17 +78,12 @@ __device__ void integrate_cell_sx(const MechView& m, const CellWs& w, const IntA
         const int nj = j + 1;
         const double h = H / nj;
         pf.start();
-        const bool okm = form_matrix<NP>(w, N, m.d.S, lane, 1.0 / h, row);
+        const bool okm = form_matrix<NP>(w, N, m.d.S, lane, 1.0 / h, M);
         pf.stop(1);
         if (!okm) { rc = 2; break; }
-        const int info = lu_factor<NP>(row, N, lane, mystep, myrdiag);
-        if (info) {
-          pf.stop(2);
-          rc = 1;
-          break;
-        }
-        const int src = permute_rows<NP>(row, N, lane, mystep, myrdiag, w.slot);
+        const int info = lu_factor<NP>(M, row, N, lane, lu, w.lu);
         pf.stop(2);
+        if (info) { rc = 1; break; }
         if (PROF) {
           ++nlu;
           nsub += nj;
@@ -103,7 +98,7 @@ __device__ void integrate_cell_sx(const MechView& m, const CellWs& w, const IntA
             pf.stop(3);
           }
           pf.start();
-          yc += lu_solve<NP>(row, N, lane, src, myrdiag, lane < N ? fv : 0.0);
+          yc += lu_solve<NP>(row, lu, lane < N ? fv : 0.0);
           pf.stop(4);
         }
         // new row of the table from the previous one

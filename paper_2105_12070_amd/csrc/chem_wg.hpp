@@ -45,7 +45,6 @@ struct WgTerms {
 
 // Per-workgroup LDS workspace (beyond the staged mechanism blob); NP = N
 // rounded up to a multiple of 16.
-typedef double dbl4 __attribute__((ext_vector_type(4)));
 typedef double dbl2 __attribute__((ext_vector_type(2)));
 
 struct WgWs {
