@@ -483,108 +483,191 @@ __device__ inline bool wg_form(const MechView& m, const WgWs& w, const double* S
   return !block_any(bad, w.flag + 1);
 }
 
+// The rare outcome of a panel's pivot search (see lu_tie): rows share the
+// largest upper half kmax.  Returns the row: largest lower half, then the
+// earliest in getrf's order, which src (lane j < k: the row of step j) gives.
+template <int NS>
+__device__ inline int panel_tie(const unsigned long long (&cand)[NS], unsigned kmax, const unsigned (&lo)[NS], int src,
+                                int k, int lane, bool& sing) {
+  unsigned best = 0;
+#pragma unroll
+  for (int s = 0; s < NS; ++s)
+#pragma clang loop unroll(disable)
+    for (unsigned long long c = cand[s]; c; c &= c - 1)
+      best = max(best, (unsigned)__builtin_amdgcn_readlane((int)lo[s], __builtin_ctzll(c)));
+  sing = (kmax | best) == 0u;
+  int pos[NS];
+#pragma unroll
+  for (int s = 0; s < NS; ++s) pos[s] = s * WAVE + lane;
+#pragma clang loop unroll(disable)
+  for (int j = 0; j < k; ++j) {
+    const int pj = __builtin_amdgcn_readlane(src, j);
+    int pp = 0;
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+      if (pj / WAVE == s) pp = __builtin_amdgcn_readlane(pos[s], pj & (WAVE - 1));
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      const int np = pos[s] == j ? pp : pos[s];
+      pos[s] = s * WAVE + lane == pj ? j : np;
+    }
+  }
+  int row = k, pmin = 1 << 20;
+#pragma unroll
+  for (int s = 0; s < NS; ++s)
+#pragma clang loop unroll(disable)
+    for (unsigned long long c = cand[s]; c; c &= c - 1) {
+      const int l = __builtin_ctzll(c);
+      const int v = __builtin_amdgcn_readlane(pos[s], l);
+      if ((unsigned)__builtin_amdgcn_readlane((int)lo[s], l) == best && v < pmin) {
+        pmin = v;
+        row = s * WAVE + l;
+      }
+    }
+  return row;
+}
+
 // Factors the panel (rows p0..NP-1, columns p0..p0+15, staged in Pn) in the
-// registers of wave 0: relative row r sits in lane r % 64, slot r / 64.  The
-// pivot is the first row with the largest |a| (exact comparison of the
-// non-negative doubles as integers, then the smallest row index); the pivot
-// row is broadcast with readlane and swapped into row kk.  Records piv, 1/U_kk
-// and a zero-pivot step in flag[2]; leaves the factored panel in Pn.
+// registers of wave 0: relative row r sits in lane r % 64, slot r / 64, and
+// stays there; at step kk the pivot is the row of largest |a| among those not
+// yet chosen (upper halves by one wave max; ties in panel_tie).  Every row's
+// reciprocal is formed while the search runs.  The interchanges are composed
+// once at the end, where the rows go back to Pn in getrf's order: afterwards
+// row sdst[i] of the matrix is old row ssrc[i].  Records piv, 1/U_kk and the
+// first zero pivot in flag[2].
+// Bound: the serial chain of wave 0 (the other waves wait).  With physical row
+// swaps, three dependent searches and the reciprocal after them a column took
+// 1,620 cycles (259k of an attempt at 151 species), PANEL_CYCLES now.
 template <int NS>
 __device__ inline void wg_panel(const WgWs& w, int p0, int NP, int lane) {
   const int nrow = NP - p0;
   double P[NS][WNB];
+  bool elig[NS];
 #pragma unroll
   for (int sl = 0; sl < NS; ++sl) {
     const int rel = sl * WAVE + lane;
+    elig[sl] = rel < nrow;
 #pragma unroll
     for (int c = 0; c < WNB; ++c) P[sl][c] = rel < nrow ? w.Pn[rel * WNB + c] : 0.0;
   }
-#pragma clang loop unroll(full)
-  for (int kk = 0; kk < WNB; ++kk) {
-    double best = -1.0;
-    int brel = 1 << 20;
+  int src = lane;      // lane kk: the row chosen at step kk
+  double rdg = 0.0;    // lane kk: 1 / U_kk
+  int first = 0;       // first zero pivot, 1-based
+  static_for<0, WNB>([&](auto Kc) __attribute__((always_inline)) {
+    constexpr int kk = decltype(Kc)::value;
+    double r[NS];
+    unsigned key[NS], m = 0;
 #pragma unroll
-    for (int sl = 0; sl < NS; ++sl) {
-      const int rel = sl * WAVE + lane;
-      const double v = fabs(P[sl][kk]);
-      if (rel >= kk && rel < nrow && v > best) {
-        best = v;
-        brel = rel;
+    for (int s = 0; s < NS; ++s) {
+      r[s] = recip(P[s][kk]);
+      const unsigned hi = (unsigned)(__builtin_bit_cast(unsigned long long, P[s][kk]) >> 32) & 0x7fffffffu;
+      key[s] = elig[s] ? hi : 0u;
+      m = max(m, key[s]);
+    }
+    const unsigned kmax = wave_max_u32(m);
+    unsigned long long cand[NS];
+    int cnt = 0, row = 0;
+#pragma unroll
+    for (int s = NS - 1; s >= 0; --s) {
+      cand[s] = ballot(key[s] == kmax);
+      cnt += __builtin_popcountll(cand[s]);
+      row = cand[s] ? s * WAVE + (int)__builtin_ctzll(cand[s]) : row;
+      asm volatile("" : "+v"(r[s]));  // keeps the reciprocals before the branch
+    }
+    bool sing = false;
+    if (__builtin_expect(cnt != 1, 0)) {
+      unsigned lo[NS];
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        lo[s] = (unsigned)__builtin_bit_cast(unsigned long long, P[s][kk]);
+        cand[s] &= ballot(elig[s]);
+      }
+      row = panel_tie<NS>(cand, kmax, lo, src, kk, lane, sing);
+      if (sing && first == 0) first = p0 + kk + 1;
+    }
+    row = uniform_int(row);
+    src = writelane(row, kk, src);
+    const int lp = row & (WAVE - 1), sp = row / WAVE;
+    // the pivot row's slot is wave-uniform: a scalar branch picks it
+    double b[WNB], rp = 0.0;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      if (NS == 1 || sp == s) {
+        rp = readlane(r[s], lp);
+#pragma unroll
+        for (int c = kk + 1; c < WNB; ++c) b[c] = readlane(P[s][c], lp);
       }
     }
-    const unsigned long long key = __builtin_bit_cast(unsigned long long, best < 0.0 ? 0.0 : best);
-    const unsigned hi = (unsigned)(key >> 32), lo = (unsigned)key;
-    const unsigned mh = wave_max_u32(best < 0.0 ? 0u : hi);
-    // the low halves decide only between lanes that tie on the high half
-    const bool top = best >= 0.0 && hi == mh;
-    bool holder = top;
-    if (__builtin_popcountll(ballot(top)) > 1) {
-      const unsigned ml = wave_max_u32(top ? lo : 0u);
-      holder = top && lo == ml;
+    rp = sing ? 0.0 : rp;
+    rdg = lane == kk ? rp : rdg;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      elig[s] = elig[s] && !(s * WAVE + lane == row);
+      const double nl = -(P[s][kk] * rp);
+      const double nlz = elig[s] ? nl : 0.0;
+      P[s][kk] = elig[s] ? -nl : P[s][kk];
+#pragma unroll
+      for (int c = kk + 1; c < WNB; ++c) P[s][c] = fma(nlz, b[c], P[s][c]);
     }
-    // first row holding the maximum: the lowest slot with a holder, then the
-    // lowest lane in it (one ballot per slot)
-    int pr = kk;
+  });
+  // the interchanges: lane i of the table: position myrow now holds row mysrc
+  // (both absolute, at most 32 touched positions)
+  int myrow = -1, mysrc = -1, nt = 0, piv = p0 + lane;
+  int np[NS];
 #pragma unroll
-    for (int sl = NS - 1; sl >= 0; --sl) {
-      const unsigned long long bm = ballot(holder && brel / WAVE == sl);
-      if (bm) pr = sl * WAVE + (int)__builtin_ctzll(bm);
-    }
-    pr = pr < nrow ? pr : kk;
-    const int lp = pr & (WAVE - 1), sp = pr / WAVE;
-    // the pivot row's slot is wave-uniform: a scalar branch picks it.  The
-    // update needs columns kk.. of the pivot row; the columns left of kk only
-    // move with a row interchange, so they are broadcast only then.
-    double b[WNB];
-#pragma unroll
-    for (int sl = 0; sl < NS; ++sl) {
-      if (sp == sl) {
-#pragma unroll
-        for (int c = kk; c < WNB; ++c) b[c] = readlane(P[sl][c], lp);
+  for (int s = 0; s < NS; ++s) np[s] = p0 + s * WAVE + lane;
+  if (ballot(lane < WNB && src != lane)) {
+#pragma clang loop unroll(disable)
+    for (int kk = 0; kk < WNB; ++kk) {
+      const int k = p0 + kk, row = p0 + __builtin_amdgcn_readlane(src, kk);
+      const unsigned long long br = ballot(mysrc == row);
+      const int q = br ? __builtin_amdgcn_readlane(myrow, (int)__builtin_ctzll(br)) : row;  // where the row is
+      piv = writelane(q, kk, piv);
+      if (q == k) continue;
+      const unsigned long long bk = ballot(myrow == k);
+      int sk = nt;
+      if (bk) sk = (int)__builtin_ctzll(bk);
+      else {
+        if (lane == nt) myrow = mysrc = k;
+        ++nt;
       }
-    }
-    const double pv = b[kk];
-    const bool sing = !(pv != 0.0);
-    if (!sing && pr != kk) {
-#pragma unroll
-      for (int sl = 0; sl < NS; ++sl) {
-        if (sp == sl) {
-#pragma unroll
-          for (int c = 0; c < kk; ++c) b[c] = readlane(P[sl][c], lp);
-        }
+      int sq = nt;
+      const unsigned long long bq = ballot(myrow == q);
+      if (bq) sq = (int)__builtin_ctzll(bq);
+      else {
+        if (lane == nt) myrow = mysrc = q;
+        ++nt;
       }
-#pragma unroll
-      for (int c = 0; c < WNB; ++c) {
-        const double a = readlane(P[0][c], kk);
-#pragma unroll
-        for (int sl = 0; sl < NS; ++sl) P[sl][c] = (lane == lp && sp == sl) ? a : P[sl][c];
-        P[0][c] = lane == kk ? b[c] : P[0][c];
-      }
+      const int srck = __builtin_amdgcn_readlane(mysrc, sk), srcq = __builtin_amdgcn_readlane(mysrc, sq);
+      if (lane == sk) mysrc = srcq;
+      if (lane == sq) mysrc = srck;
     }
-    const double rp = sing ? 0.0 : recip(pv);
-    if (lane == 0) {
-      w.piv[p0 + kk] = (sing ? kk : pr) + p0;
-      w.rdg[p0 + kk] = rp;
-      if (sing && w.flag[2] == 0) w.flag[2] = p0 + kk + 1;
-    }
+#pragma clang loop unroll(disable)
+    for (int i = 0; i < nt; ++i) {
+      const int d = __builtin_amdgcn_readlane(myrow, i), o = __builtin_amdgcn_readlane(mysrc, i);
 #pragma unroll
-    for (int sl = 0; sl < NS; ++sl) {
-      const int rel = sl * WAVE + lane;
-      if (rel > kk && rel < nrow) {
-        const double l = P[sl][kk] * rp;
-        P[sl][kk] = l;
-#pragma clang loop unroll(full)
-        for (int c = kk + 1; c < WNB; ++c) P[sl][c] = fma(-l, b[c], P[sl][c]);
-      }
+      for (int s = 0; s < NS; ++s) np[s] = p0 + s * WAVE + lane == o ? d : np[s];
     }
   }
 #pragma unroll
   for (int sl = 0; sl < NS; ++sl) {
-    const int rel = sl * WAVE + lane;
-    if (rel < nrow) {
+    if (sl * WAVE + lane < nrow) {
+      double* Pr = w.Pn + (np[sl] - p0) * WNB;
 #pragma unroll
-      for (int c = 0; c < WNB; ++c) w.Pn[rel * WNB + c] = P[sl][c];
+      for (int c = 0; c < WNB; ++c) Pr[c] = P[sl][c];
     }
+  }
+  if (lane < WNB) {
+    w.piv[p0 + lane] = piv;
+    w.rdg[p0 + lane] = rdg;
+  }
+  if (lane < nt) {
+    w.sdst[lane] = myrow;
+    w.ssrc[lane] = mysrc;
+  }
+  if (lane == 0) {
+    w.flag[4] = nt;
+    if (first && w.flag[2] == 0) w.flag[2] = first;
   }
   wsync();
 }
@@ -636,6 +719,39 @@ __device__ inline void wg_panel_lds(const WgWs& w, int p0, int NP, int lane) {
   }
 }
 
+// The 16 interchanges piv of the panel at p0 composed on the rows they touch (at
+// most 32, one per lane): afterwards row sdst[i] holds old row ssrc[i].
+__device__ inline void wg_compose(const WgWs& w, int p0, int lane) {
+  int myrow = -1, mysrc = -1, nt = 0;
+#pragma clang loop unroll(disable)
+  for (int kk = 0; kk < WNB; ++kk) {
+    const int k = p0 + kk, q = w.piv[k];
+    if (q == k) continue;
+    const unsigned long long bk = ballot(myrow == k);
+    int sk = nt;
+    if (bk) sk = (int)__builtin_ctzll(bk);
+    else {
+      if (lane == nt) myrow = mysrc = k;
+      ++nt;
+    }
+    const unsigned long long bq = ballot(myrow == q);
+    int sq = nt;
+    if (bq) sq = (int)__builtin_ctzll(bq);
+    else {
+      if (lane == nt) myrow = mysrc = q;
+      ++nt;
+    }
+    const int srck = __builtin_amdgcn_readlane(mysrc, sk), srcq = __builtin_amdgcn_readlane(mysrc, sq);
+    if (lane == sk) mysrc = srcq;
+    if (lane == sq) mysrc = srck;
+  }
+  if (lane < nt) {
+    w.sdst[lane] = myrow;
+    w.ssrc[lane] = mysrc;
+  }
+  if (lane == 0) w.flag[4] = nt;
+}
+
 // Blocked LU with partial pivoting of Mx in place.  Returns the 1-based step
 // of a zero pivot column, or 0.  Leaves piv, perm and 1/U_kk in LDS.
 template <bool PROF = false>
@@ -667,37 +783,10 @@ __device__ inline int wg_lu(const WgWs& w, double* Mx, int NP, Prof<PROF>* pf = 
       if (nrow <= WAVE) wg_panel<1>(w, p0, NP, lane);
       else if (nrow <= 2 * WAVE) wg_panel<2>(w, p0, NP, lane);
       else if (nrow <= 3 * WAVE) wg_panel<3>(w, p0, NP, lane);
-      else wg_panel_lds(w, p0, NP, lane);
-      // the panel's 16 interchanges composed on the rows they touch (at most
-      // 32, one per lane): afterwards row sdst[i] holds old row ssrc[i]
-      int myrow = -1, mysrc = -1, nt = 0;
-#pragma clang loop unroll(disable)
-      for (int kk = 0; kk < WNB; ++kk) {
-        const int k = p0 + kk, q = w.piv[k];
-        if (q == k) continue;
-        const unsigned long long bk = ballot(myrow == k);
-        int sk = nt;
-        if (bk) sk = (int)__builtin_ctzll(bk);
-        else {
-          if (lane == nt) myrow = mysrc = k;
-          ++nt;
-        }
-        const unsigned long long bq = ballot(myrow == q);
-        int sq = nt;
-        if (bq) sq = (int)__builtin_ctzll(bq);
-        else {
-          if (lane == nt) myrow = mysrc = q;
-          ++nt;
-        }
-        const int srck = __builtin_amdgcn_readlane(mysrc, sk), srcq = __builtin_amdgcn_readlane(mysrc, sq);
-        if (lane == sk) mysrc = srcq;
-        if (lane == sq) mysrc = srck;
+      else {
+        wg_panel_lds(w, p0, NP, lane);
+        wg_compose(w, p0, lane);
       }
-      if (lane < nt) {
-        w.sdst[lane] = myrow;
-        w.ssrc[lane] = mysrc;
-      }
-      if (lane == 0) w.flag[4] = nt;
     }
     __syncthreads();
     if (PROF) {
@@ -710,12 +799,14 @@ __device__ inline int wg_lu(const WgWs& w, double* Mx, int NP, Prof<PROF>* pf = 
 #pragma clang loop unroll(disable)
     for (int j = t; j < NP; j += WG) {
       if (j >= p0 && j < p0 + WNB) continue;
-      double v[2 * WNB];
+      if (nsw) {
+        double v[2 * WNB];
 #pragma unroll
-      for (int i = 0; i < 2 * WNB; ++i) v[i] = i < nsw ? Mx[(size_t)w.ssrc[i] * NP + j] : 0.0;
+        for (int i = 0; i < 2 * WNB; ++i) v[i] = i < nsw ? Mx[(size_t)w.ssrc[i] * NP + j] : 0.0;
 #pragma unroll
-      for (int i = 0; i < 2 * WNB; ++i)
-        if (i < nsw) Mx[(size_t)w.sdst[i] * NP + j] = v[i];
+        for (int i = 0; i < 2 * WNB; ++i)
+          if (i < nsw) Mx[(size_t)w.sdst[i] * NP + j] = v[i];
+      }
       // rows of U of this panel: U12 = L11^-1 A12 (column j, forward substitution)
       if (j >= p0 + WNB) {
         double u[WNB];
