@@ -537,7 +537,8 @@ __device__ inline int panel_tie(const unsigned long long (&cand)[NS], unsigned k
 // first zero pivot in flag[2].
 // Bound: the serial chain of wave 0 (the other waves wait).  With physical row
 // swaps, three dependent searches and the reciprocal after them a column took
-// 1,620 cycles (259k of an attempt at 151 species), PANEL_CYCLES now.
+// 1,510 cycles (241k of an attempt at 151 species, two workgroups a CU); now
+// 950 (152k).
 template <int NS>
 __device__ inline void wg_panel(const WgWs& w, int p0, int NP, int lane) {
   const int nrow = NP - p0;
