@@ -855,11 +855,10 @@ __device__ inline int ros_attempt(const MechView& m, const CellWs& w, const RosT
   double fi = f0;
 #pragma clang loop unroll(disable)
   for (int i = 0; i < s; ++i) {
-    // contributions of K_{i-1}, K_{i-2}, K_{i-3}
-    const double a0 = i >= 1 ? tab.a[i][i - 1] : 0.0, c0 = i >= 1 ? tab.c[i][i - 1] : 0.0;
-    const double a1 = i >= 2 ? tab.a[i][i - 2] : 0.0, c1 = i >= 2 ? tab.c[i][i - 2] : 0.0;
-    const double a2 = i >= 3 ? tab.a[i][i - 3] : 0.0, c2 = i >= 3 ? tab.c[i][i - 3] : 0.0;
-    if (i > 0 && tab.newf[i]) {
+    // contributions of K_{i-1}, K_{i-2}, K_{i-3}, one aligned row per stage
+    const RosStage st = tab.stage[i];
+    const double a0 = st.a[0], a1 = st.a[1], a2 = st.a[2], c0 = st.c[0], c1 = st.c[1], c2 = st.c[2];
+    if (st.newf) {
       const double Yi = y + a0 * K0 + a1 * K1 + a2 * K2;
       pf.start();
       fi = rhs(m, w, lane < N ? Yi : 0.0, p, lane);
@@ -881,10 +880,8 @@ __device__ inline int ros_attempt(const MechView& m, const CellWs& w, const RosT
     kst[3] = K0;
   }
   // after s stages K0 = K_{s-1}, K1 = K_{s-2}, ...
-  const double m0 = tab.m[s - 1], e0 = tab.e[s - 1];
-  const double m1 = s >= 2 ? tab.m[s - 2] : 0.0, e1 = s >= 2 ? tab.e[s - 2] : 0.0;
-  const double m2 = s >= 3 ? tab.m[s - 3] : 0.0, e2 = s >= 3 ? tab.e[s - 3] : 0.0;
-  const double m3 = s >= 4 ? tab.m[s - 4] : 0.0, e3 = s >= 4 ? tab.e[s - 4] : 0.0;
+  const double m0 = tab.mr[0], m1 = tab.mr[1], m2 = tab.mr[2], m3 = tab.mr[3];
+  const double e0 = tab.er[0], e1 = tab.er[1], e2 = tab.er[2], e3 = tab.er[3];
   ynew = y + (m0 * K0 + m1 * K1 + m2 * K2 + m3 * K3);
   err = e0 * K0 + e1 * K1 + e2 * K2 + e3 * K3;
   return 0;
