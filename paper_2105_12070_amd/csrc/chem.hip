@@ -133,33 +133,49 @@ __global__ void k_reset(int* q, unsigned long long* failed) {
   }
 }
 
-template <int NP>
+// f (and J, if given) of every cell, one cell per wave.  WALK: the grid fills
+// the chip once and walks the cells, so a workgroup stages its tables once.  J
+// leaves LDS in address order: with a row per lane each store of a wave touched
+// 55 lines 440 bytes apart.
+// Bound: the waves that fit (jac_pass is a chain through LDS; J's block limits a
+// CU to four), the 726 MB of J of 30,000 cells of 54 species take 160 us at the
+// rate of a copy.  One row per lane, tables staged for every four cells: 909
+// us; now 712.  f alone keeps no J block, so twice the waves fit: 60,000 cells
+// 486 -> 252 us.
+template <int NP, bool WALK>
 __global__ __launch_bounds__(max_threads<NP>()) void k_rhs_jac(IntArgs a, const double* st, double* f, double* J) {
   extern __shared__ __align__(16) uint8_t lds[];
   stage_blob(lds, a.blob, a.d.lds_bytes);
   const MechView m = make_view(lds, a);
-  const int wv = threadIdx.x / WAVE;
-  const CellWs w = make_ws((double*)(lds + a.d.lds_bytes) + (size_t)wv * a.cell_doubles, a.d);
-  const int64_t c = (int64_t)blockIdx.x * (blockDim.x / WAVE) + wv;
-  if (c >= a.ncells) return;
+  const int wv = threadIdx.x / WAVE, wpb = blockDim.x / WAVE;
+  const CellWs w = make_ws((double*)(lds + a.d.lds_bytes) + (size_t)wv * a.cell_doubles, a.d, J != nullptr);
   const int lane = lane_id();
-  const int N = m.d.N;
+  const int N = m.d.N, S = m.d.S;
   if (lane == 0) {
     w.C[m.d.K] = 1.0;
     w.g[m.d.K] = 0.0;
     w.hR[m.d.K] = 0.0;
   }
   wsync();
-  const double y = lane < N ? st[(int64_t)lane * a.ld + c] : 0.0;
-  double fv;
-  if (J) {
-    fv = jac_pass<NP>(m, w, y, a.p, lane);
-    if (lane < N)
-      for (int j = 0; j < N; ++j) J[((size_t)c * N + lane) * N + j] = w.J[lane * m.d.S + j];
-  } else {
-    fv = rhs(m, w, y, a.p, lane);
+#pragma clang loop unroll(disable)
+  for (int64_t c = (int64_t)blockIdx.x * wpb + wv; c < a.ncells; c += (int64_t)gridDim.x * wpb) {
+    const double y = lane < N ? st[(int64_t)lane * a.ld + c] : 0.0;
+    double fv;
+    if (J) {
+      fv = jac_pass<NP>(m, w, y, a.p, lane);
+      const int rows = WAVE / N, r0 = lane / N, col = lane - r0 * N;  // rows per store, the lane's row and column
+      double* Jc = J + (size_t)c * N * N;
+      if (r0 < rows) {
+#pragma clang loop unroll_count(4)
+        for (int i = r0; i < N; i += rows) Jc[i * N + col] = w.J[i * S + col];
+      }
+    } else {
+      fv = rhs(m, w, y, a.p, lane);
+    }
+    if (f && lane < N) f[(int64_t)lane * a.ld + c] = fv;
+    if (!WALK) break;
+    wsync();
   }
-  if (f && lane < N) f[(int64_t)lane * a.ld + c] = fv;
 }
 
 template <int NP>
@@ -774,6 +790,40 @@ int launch_integrate(chem_mech* m, const IntArgs& a0, const Variant& v, hipStrea
       hipLaunchKernelGGL(kern, dim3(grid), dim3(wpb * WAVE), lds, s, a);
       HIPCHK(hipGetLastError());
     }
+    return 0;
+  });
+}
+
+// f (and J unless null) of every cell.  Without J a wave needs no Jacobian block.
+int launch_rhs_jac(const chem_mech* m, const IntArgs& a0, const double* state, double* f, double* J, hipStream_t s) {
+  if (m->wg) return launch_rhs_jac_wg(const_cast<chem_mech*>(m), a0, state, f, J, s);
+  IntArgs a = a0;
+  if (!J) a.cell_doubles = wave_rates_doubles(m->d.R, m->d.R0);
+  const int wpb = std::max(1, std::min(4, max_wpb(m)));
+  const size_t lds = m->d.lds_bytes + (size_t)wpb * a.cell_doubles * sizeof(double);
+  return with_np(m->d.N, [&](auto npc) -> int {
+    constexpr int NP = decltype(npc)::value;
+    const int64_t need = (a.ncells + wpb - 1) / wpb;
+    int64_t grid = need;
+    auto kern = k_rhs_jac<NP, false>;
+    // Walk where the cells exceed one fill of the chip: the tables are staged
+    // once instead of once per four cells.  The loop costs registers (121 ->
+    // 173), so calls that fit keep one cell per wave (f of 1,000 cells of 54
+    // species: 10.5 us, walking 11.2), and so do up to 15 species, whose tables
+    // are small and whose waves the registers limit (f of 60,000 cells of 10:
+    // 80 us, walking 100; their J of 16,000: 45 and 60).
+    if constexpr (NP > 16) {
+      int occ = 0;
+      HIPCHK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_rhs_jac<NP, true>, wpb * WAVE, lds));
+      const int64_t fill = (int64_t)m->ncu * std::max(occ, 1);
+      if (need > fill) {
+        grid = fill;
+        kern = k_rhs_jac<NP, true>;
+      }
+    }
+    if (set_lds_limit<NP>((const void*)kern, lds)) return CHEM_EHIP;
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(wpb * WAVE), lds, s, a, state, f, J);
+    HIPCHK(hipGetLastError());
     return 0;
   });
 }
@@ -1507,17 +1557,7 @@ int chem_rhs(const chem_mech* m, int64_t ncells, int64_t ld, const double* state
   a.ld = ld;
   a.ncells = ncells;
   a.p = 10.0 * p;
-  if (m->wg) return launch_rhs_jac_wg(const_cast<chem_mech*>(m), a, state, f, nullptr, (hipStream_t)stream);
-  const int wpb = std::max(1, std::min(4, max_wpb(m)));
-  const size_t lds = m->d.lds_bytes + (size_t)wpb * cell_bytes(m->d);
-  return with_np(m->d.N, [&](auto npc) -> int {
-    constexpr int NP = decltype(npc)::value;
-    if (set_lds_limit<NP>((const void*)k_rhs_jac<NP>, lds)) return CHEM_EHIP;
-    hipLaunchKernelGGL(k_rhs_jac<NP>, dim3((ncells + wpb - 1) / wpb), dim3(wpb * WAVE), lds, (hipStream_t)stream, a,
-                       state, f, (double*)nullptr);
-    HIPCHK(hipGetLastError());
-    return 0;
-  });
+  return launch_rhs_jac(m, a, state, f, nullptr, (hipStream_t)stream);
 }
 
 int chem_jacobian(const chem_mech* m, int64_t ncells, int64_t ld, const double* state, double p, double* J,
@@ -1529,17 +1569,7 @@ int chem_jacobian(const chem_mech* m, int64_t ncells, int64_t ld, const double* 
   a.ld = ld;
   a.ncells = ncells;
   a.p = 10.0 * p;
-  if (m->wg) return launch_rhs_jac_wg(const_cast<chem_mech*>(m), a, state, f, J, (hipStream_t)stream);
-  const int wpb = std::max(1, std::min(4, max_wpb(m)));
-  const size_t lds = m->d.lds_bytes + (size_t)wpb * cell_bytes(m->d);
-  return with_np(m->d.N, [&](auto npc) -> int {
-    constexpr int NP = decltype(npc)::value;
-    if (set_lds_limit<NP>((const void*)k_rhs_jac<NP>, lds)) return CHEM_EHIP;
-    hipLaunchKernelGGL(k_rhs_jac<NP>, dim3((ncells + wpb - 1) / wpb), dim3(wpb * WAVE), lds, (hipStream_t)stream, a,
-                       state, f, J);
-    HIPCHK(hipGetLastError());
-    return 0;
-  });
+  return launch_rhs_jac(m, a, state, f, J, (hipStream_t)stream);
 }
 
 // Workgroup LU (64 < n <= 256): one matrix per 256-thread workgroup, an
