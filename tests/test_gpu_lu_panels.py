@@ -65,3 +65,23 @@ def test_panels_match_elimination(chem, n, kind):
         # the solve's residual: backward error of a pivoted LU solve
         res = np.abs(A[m] @ x[m] - b[m]).max()
         assert res <= 10 * n * EPS * (np.abs(A[m]).sum(1).max() * np.abs(x[m]).max() + np.abs(b[m]).max())
+
+
+@pytest.mark.parametrize("kind", ["random", "dominant", "reversed"])
+@pytest.mark.parametrize("n", [65, 80, 127, 128, 129, 143, 160, 161, 192, 193, 208, 255, 256])
+def test_workgroup_panels_backward_error(chem, n, kind):
+    """Above 64: sizes at the edges of the panel's register slots (64, 128, 192 rows) and of its 16 columns, with many,
+    all and no interchanges.  |P A - L U| <= gamma_n |L| |U| entry by entry holds for any order of the elimination's
+    sums (Higham, Accuracy and Stability, Theorem 9.3); the multiplication by a rounded reciprocal and the residual's
+    own sums add as much again: (2 n + 8) eps |L| |U|."""
+    A = matrices(n, kind, np.random.default_rng(1900 + n))
+    LU, ipiv, info = chem.lu_factor(torch.tensor(A, device=DEV))
+    LU, ipiv = LU.cpu().numpy(), ipiv.cpu().numpy()
+    assert np.all(info.cpu().numpy() == 0)
+    for m in range(5):
+        np.testing.assert_array_equal(ipiv[m], getrf(A[m])[1])
+        PA = A[m].copy()
+        for k, p in enumerate(ipiv[m]):
+            PA[[k, p]] = PA[[p, k]]
+        L, U = np.tril(LU[m], -1) + np.eye(n), np.triu(LU[m])
+        assert np.all(np.abs(PA - L @ U) <= (2 * n + 8) * EPS * (np.abs(L) @ np.abs(U)))
