@@ -483,19 +483,37 @@ __device__ inline bool wg_form(const MechView& m, const WgWs& w, const double* S
   return !block_any(bad, w.flag + 1);
 }
 
-// The rare outcome of a panel's pivot search (see lu_tie): rows share the
-// largest upper half kmax.  Returns the row: largest lower half, then the
-// earliest in getrf's order, which src (lane j < k: the row of step j) gives.
+// The rare outcomes of a panel's pivot search: rows share the largest upper half
+// (see lu_tie), or the largest is Inf or NaN.  v: the column's values, elig: the
+// rows not yet chosen.  NaN is passed over, as idamax's comparisons do (the
+// integer keys of the common search would make it the largest): the pivot is the
+// largest |v| of the others, and only a column of nothing but NaN takes its
+// first row.  Returns the row: largest |v|, then the earliest in getrf's order,
+// which src (lane j < k: the row of step j) gives.
 template <int NS>
-__device__ inline int panel_tie(const unsigned long long (&cand)[NS], unsigned kmax, const unsigned (&lo)[NS], int src,
-                                int k, int lane, bool& sing) {
+__device__ inline int panel_tie(const double (&v)[NS], const bool (&elig)[NS], int src, int k, int lane, bool& sing) {
+  unsigned hi[NS], lo[NS], m = 0;
+  bool num[NS];
+  unsigned long long cand[NS], any = 0;
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, v[s]);
+    num[s] = elig[s] && !__builtin_isnan(v[s]);
+    any |= ballot(num[s]);
+    hi[s] = num[s] ? (unsigned)(u >> 32) & 0x7fffffffu : 0u;
+    lo[s] = num[s] ? (unsigned)u : 0u;
+    m = max(m, hi[s]);
+  }
+  const unsigned kmax = wave_max_u32(m);
+#pragma unroll
+  for (int s = 0; s < NS; ++s) cand[s] = ballot(elig[s] && (num[s] || !any) && hi[s] == kmax);
   unsigned best = 0;
 #pragma unroll
   for (int s = 0; s < NS; ++s)
 #pragma clang loop unroll(disable)
     for (unsigned long long c = cand[s]; c; c &= c - 1)
       best = max(best, (unsigned)__builtin_amdgcn_readlane((int)lo[s], __builtin_ctzll(c)));
-  sing = (kmax | best) == 0u;
+  sing = any && (kmax | best) == 0u;
   int pos[NS];
 #pragma unroll
   for (int s = 0; s < NS; ++s) pos[s] = s * WAVE + lane;
@@ -518,9 +536,9 @@ __device__ inline int panel_tie(const unsigned long long (&cand)[NS], unsigned k
 #pragma clang loop unroll(disable)
     for (unsigned long long c = cand[s]; c; c &= c - 1) {
       const int l = __builtin_ctzll(c);
-      const int v = __builtin_amdgcn_readlane(pos[s], l);
-      if ((unsigned)__builtin_amdgcn_readlane((int)lo[s], l) == best && v < pmin) {
-        pmin = v;
+      const int at = __builtin_amdgcn_readlane(pos[s], l);
+      if ((unsigned)__builtin_amdgcn_readlane((int)lo[s], l) == best && at < pmin) {
+        pmin = at;
         row = s * WAVE + l;
       }
     }
@@ -530,11 +548,11 @@ __device__ inline int panel_tie(const unsigned long long (&cand)[NS], unsigned k
 // Factors the panel (rows p0..NP-1, columns p0..p0+15, staged in Pn) in the
 // registers of wave 0: relative row r sits in lane r % 64, slot r / 64, and
 // stays there; at step kk the pivot is the row of largest |a| among those not
-// yet chosen (upper halves by one wave max; ties in panel_tie).  Every row's
-// reciprocal is formed while the search runs.  The interchanges are composed
-// once at the end, where the rows go back to Pn in getrf's order: afterwards
-// row sdst[i] of the matrix is old row ssrc[i].  Records piv, 1/U_kk and the
-// first zero pivot in flag[2].
+// yet chosen (upper halves by one wave max; ties and columns with Inf or NaN in
+// panel_tie).  Every row's reciprocal is formed while the search runs.  The
+// interchanges are composed once at the end, where the rows go back to Pn in
+// getrf's order: afterwards row sdst[i] of the matrix is old row ssrc[i].
+// Records piv, 1/U_kk and the first zero pivot in flag[2].
 // Bound: the serial chain of wave 0 (the other waves wait).  With physical row
 // swaps, three dependent searches and the reciprocal after them a column took
 // 1,510 cycles (241k of an attempt at 151 species, two workgroups a CU); now
@@ -576,14 +594,11 @@ __device__ inline void wg_panel(const WgWs& w, int p0, int NP, int lane) {
       asm volatile("" : "+v"(r[s]));  // keeps the reciprocals before the branch
     }
     bool sing = false;
-    if (__builtin_expect(cnt != 1, 0)) {
-      unsigned lo[NS];
+    if (__builtin_expect(cnt != 1 || kmax >= 0x7ff00000u, 0)) {
+      double v[NS];
 #pragma unroll
-      for (int s = 0; s < NS; ++s) {
-        lo[s] = (unsigned)__builtin_bit_cast(unsigned long long, P[s][kk]);
-        cand[s] &= ballot(elig[s]);
-      }
-      row = panel_tie<NS>(cand, kmax, lo, src, kk, lane, sing);
+      for (int s = 0; s < NS; ++s) v[s] = P[s][kk];
+      row = panel_tie<NS>(v, elig, src, kk, lane, sing);
       if (sing && first == 0) first = p0 + kk + 1;
     }
     row = uniform_int(row);
@@ -604,11 +619,14 @@ __device__ inline void wg_panel(const WgWs& w, int p0, int NP, int lane) {
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       elig[s] = elig[s] && !(s * WAVE + lane == row);
-      const double nl = -(P[s][kk] * rp);
-      const double nlz = elig[s] ? nl : 0.0;
-      P[s][kk] = elig[s] ? -nl : P[s][kk];
+      // only the rows still open: 0 times an Inf or NaN of the pivot row would
+      // spoil a finished row of U
+      if (elig[s]) {
+        const double l = P[s][kk] * rp;
+        P[s][kk] = l;
 #pragma unroll
-      for (int c = kk + 1; c < WNB; ++c) P[s][c] = fma(nlz, b[c], P[s][c]);
+        for (int c = kk + 1; c < WNB; ++c) P[s][c] = fma(-l, b[c], P[s][c]);
+      }
     }
   });
   // the interchanges: lane i of the table: position myrow now holds row mysrc
