@@ -210,7 +210,7 @@ __global__ __launch_bounds__(256, 2) void k_lu_factor(int64_t nmat, int n, const
   load_tiles<NP>(A + (size_t)mi * n * n, n, lane, M);
   double row[NP];
   LuPiv<NP> lu;
-  const int rc = lu_factor<NP>(M, row, n, lane, lu, scr[wv]);
+  const int rc = lu_factor<NP, true>(M, row, n, lane, lu, scr[wv]);
   if (lane == 0) info[mi] = rc;
   if (rc) return;  // some rows never became pivots: no permutation to apply
   if (lane < n) {

@@ -603,7 +603,11 @@ struct MatTiles {
 // Measured for N = 55 (shader cycles of one factorisation, two waves per SIMD /
 // one wave): 87.9k / 67.5k row-per-lane with the rows permuted at the end, 54.7k /
 // 42.3k this way (a solve with the factors 5.7k / 5.2k -> 2.9k / 2.2k).
-template <int NP>
+// FACTORS: the factors are the result, and a NaN stays in the rows and columns
+// that the elimination takes it to.  A solve needs no such care (a NaN
+// multiplier makes every x NaN), and the integrators have no register for it
+// (k_adjoint<56> would go from 12 to 1,244 bytes of scratch).
+template <int NP, bool FACTORS = false>
 __device__ __forceinline__ int lu_factor(MatTiles<NP>& M, double (&row)[NP], int N, int lane, LuPiv<NP>& f, double* ub,
                                          bool nopiv = false) {
   constexpr int NG = NP / 4, NT = MatTiles<NP>::NT;  // column groups; row and column tiles
@@ -719,6 +723,23 @@ __device__ __forceinline__ int lu_factor(MatTiles<NP>& M, double (&row)[NP], int
         for (int q = 1; q < 4; ++q)
 #pragma unroll
           for (int j = 0; j < q; ++j) u[q] = fma(readlane(nl[j], p[q]), u[j], u[q]);
+        // A NaN among a row's multipliers (input that is not finite, a pivot below
+        // the normal range) makes its open columns NaN.  The update would take it
+        // to finished columns too (NaN times their 0): the row sits it out, and
+        // the finished columns of U are 0 again where the substitution met one.
+        unsigned long long bad = 0;
+        if constexpr (FACTORS) {
+          const bool num = __builtin_isfinite(nl[0] + nl[1] + nl[2] + nl[3]);
+          bad = ballot(!num);
+          if (__builtin_expect(bad != 0ull, 0)) {
+            const bool done = (lane >> 4) == tc && (ucol & 15) < 4 * v + 4;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              nl[q] = num ? nl[q] : 0.0;
+              u[q] = done ? 0.0 : u[q];
+            }
+          }
+        }
         block_transpose(u);   // -> operand A of column tile c, lane i: U[k0 + i / 16][16 c + i % 16]
         block_transpose(nl);  // -> operand B of row tile t, lane i: -L[16 t + i % 16][k0 + i / 16]
         // The lane swaps write both operands, and the compiler (ROCm 7.2) does not
@@ -739,6 +760,17 @@ __device__ __forceinline__ int lu_factor(MatTiles<NP>& M, double (&row)[NP], int
             });
           }
         });
+        if (FACTORS && __builtin_expect(bad != 0ull, 0)) {
+          static_for<0, NT>([&](auto Tc) __attribute__((always_inline)) {
+            constexpr int t = decltype(Tc)::value;
+            if ((bad >> (16 * t + n16)) & 1ull) {
+              static_for<g0, 4 * NT>([&](auto Gc) __attribute__((always_inline)) {
+                constexpr int g = decltype(Gc)::value;
+                if (g >= g0 + 4 || g < g0 + 3 - v) X[t][g] = __builtin_nan("");
+              });
+            }
+          });
+        }
       }
     }
   });

@@ -88,4 +88,57 @@ def test_workgroup_lu(chem, n, kind):
     fin = np.isfinite(ref)
     np.testing.assert_array_equal(ipiv[1], piv)
     assert np.isfinite(LU[1][fin]).all()
-    assert np.abs(LU[1] - ref)[fin].max() <= 4 * n * EPS * np.abs(ref[fin]).max()
+    assert np.abs(LU[1][fin] - ref[fin]).max() <= 4 * n * EPS * np.abs(ref[fin]).max()
+
+
+def getrf_wave(A):
+    """The wavefront LU's rules (n <= 64): NaN is the largest of all, the first of them; the reciprocal of a pivot that
+    is Inf, NaN or below the normal range is NaN; every row takes part in the updates, those already chosen with a
+    multiplier of 0."""
+    M, n = A.copy(), A.shape[0]
+    piv = np.zeros(n, np.int32)
+    with np.errstate(all="ignore"):
+        for k in range(n):
+            p = k + int(np.argmax(np.abs(M[k:, k])))  # numpy's argmax takes the first NaN
+            piv[k] = p
+            M[[k, p]] = M[[p, k]]
+            a = abs(M[k, k])
+            M[k + 1:, k] *= 1.0 / M[k, k] if np.finfo(np.float64).tiny <= a < np.inf else np.nan
+            M[k + 1:, k + 1:] -= np.outer(M[k + 1:, k], M[k, k + 1:])
+            M[:k + 1, k + 1:] -= np.outer(np.zeros(k + 1), M[k, k + 1:])
+    return M, piv
+
+
+def spoiled_wave(n, kind):
+    A = np.random.default_rng(3300 + n).standard_normal((n, n))
+    if kind.endswith("dominant"):
+        A += 3.0 * n * np.eye(n)
+    i = n // 2
+    if kind.startswith("nan_entry"):
+        A[i, i] = np.nan
+    elif kind.startswith("inf_entry"):
+        A[i, i] = np.inf
+    elif kind.startswith("subnormal_column"):
+        A[:, i] *= 1e-316
+    elif kind.startswith("nan_late"):
+        A[:, n - 1] = np.nan
+    return A
+
+
+@pytest.mark.parametrize("kind", [a + b for a in ("nan_entry", "inf_entry", "subnormal_column", "nan_late")
+                                  for b in ("", "_dominant")])
+@pytest.mark.parametrize("n", [2, 5, 16, 17, 33, 55, 56, 57, 64])
+def test_wavefront_factors(chem, n, kind):
+    """Columns finished before the NaN arose stay as they are, also within the 16-column tile that it arises in."""
+    A = spoiled_wave(n, kind)
+    good = np.random.default_rng(3400 + n).standard_normal((n, n))
+    LU, ipiv, info = (t.cpu().numpy() for t in chem.lu_factor(torch.tensor(np.stack([good, A, good]), device=DEV)))
+    ref, piv = getrf_wave(A)
+    np.testing.assert_array_equal(info, 0)
+    np.testing.assert_array_equal(LU[0], LU[2])
+    assert np.isfinite(LU[0]).all()
+    fin = np.isfinite(ref)
+    first_nan = int(np.argmax(np.isnan(ref).any(0))) if np.isnan(ref).any() else n
+    np.testing.assert_array_equal(ipiv[1][:first_nan + 1], piv[:first_nan + 1])
+    assert np.isfinite(LU[1][fin]).all()
+    assert np.abs(LU[1][fin] - ref[fin]).max() <= 4 * n * EPS * np.abs(ref[fin]).max()
