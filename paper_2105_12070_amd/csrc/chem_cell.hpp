@@ -521,47 +521,35 @@ struct LuPiv {
   __device__ __forceinline__ int piv(int k) const { return (int)((pk[k / 4] >> (8 * (k % 4))) & 63u); }
 };
 
-// Where getrf holds this lane's row before step k: the interchanges
-// j <-> position of piv(j) of the earlier steps, replayed (src: lane j < k holds piv(j)).
-__device__ inline int getrf_pos(int src, int k, int lane) {
-  int pos = lane;
+// The outcomes of a pivot search other than one lane of largest upper half kmax:
+// several share it (c), or no row is left (a padding step: the pivot is lane k).
+// The largest lower half decides, then getrf's row order.  Returns a mask whose
+// lowest lane is the pivot; records a zero pivot.
+// getrf holds a row not yet chosen at the first x >= k of x = row, piv(row),
+// piv(piv(row)), ...: step j puts the row at j where row piv(j) was (src: lane
+// j < k holds piv(j)).  A row already chosen may lie on a cycle.
+// Bound: the chain of the two reductions.  Matrices of a few magnitudes tie in
+// most columns: walking the tied lanes and replaying the interchanges took
+// 1,753 us for 20,000 periodic second differences of 64 (829 with the order kept
+// up at every step), now 809; +-1 matrices of 55, solved, 574 (471), now 381.
+__device__ inline unsigned long long lu_tie(bool elig, bool c, unsigned kmax, unsigned lo, int src, int k, int lane,
+                                            int& info) {
+  if (!ballot(elig)) return 1ull << k;
+  c = c && elig;
+  const unsigned lmax = wave_max_u32(c ? lo : 0u);
+  c = c && lo == lmax;
+  const unsigned long long cand = ballot(c);
+  if ((kmax | lmax) == 0u && info == 0) info = k + 1;
+  if ((cand & (cand - 1)) == 0ull) return cand;
+  int x = c ? lane : k;
 #pragma clang loop unroll(disable)
-  for (int j = 0; j < k; ++j) {
-    const int pj = __builtin_amdgcn_readlane(src, j), pp = __builtin_amdgcn_readlane(pos, pj);
-    const int np = pos == j ? pp : pos;
-    pos = lane == pj ? j : np;
+  for (int i = 0; i < k && ballot(x < k); ++i) {
+    const int y = __builtin_amdgcn_ds_bpermute(4 * x, src);
+    x = x < k ? y : x;
   }
-  return pos;
-}
-
-// The rare outcome of a pivot search: the lanes of cand share the largest upper
-// half kmax of |a|.  The largest lower half decides, then getrf's row order.
-// Returns a mask whose lowest lane is the pivot; records a zero pivot.  With no
-// row left (a padding step) the pivot is lane k.
-__device__ inline unsigned long long lu_tie(unsigned long long cand, unsigned kmax, unsigned lo, int src, int k,
-                                            int lane, int& info) {
-  if (!cand) return 1ull << k;
-  unsigned best = 0;
-  unsigned long long top = 0;
-#pragma clang loop unroll(disable)
-  for (; cand; cand &= cand - 1) {
-    const unsigned v = (unsigned)__builtin_amdgcn_readlane((int)lo, __builtin_ctzll(cand));
-    const unsigned long long bit = cand & (0ull - cand);
-    top = v > best ? bit : (v == best ? top | bit : top);
-    best = v > best ? v : best;
-  }
-  if ((kmax | best) == 0u && info == 0) info = k + 1;
-  if ((top & (top - 1)) == 0ull) return top;
-  const int pos = getrf_pos(src, k, lane);
-  int pmin = 64;
-  unsigned long long first = 0;
-#pragma clang loop unroll(disable)
-  for (; top; top &= top - 1) {
-    const int v = __builtin_amdgcn_readlane(pos, __builtin_ctzll(top));
-    first = v < pmin ? top & (0ull - top) : first;
-    pmin = v < pmin ? v : pmin;
-  }
-  return first;
+  const unsigned early = c ? (unsigned)(WAVE - x) : 0u;
+  const unsigned first = wave_max_u32(early);  // of all lanes, not behind the &&
+  return ballot(c && early == first);
 }
 
 // Doubles of the LDS scratch that lu_factor uses (four rows of U).
@@ -644,12 +632,13 @@ __device__ __forceinline__ int lu_factor(MatTiles<NP>& M, double (&row)[NP], int
           const unsigned hi = (unsigned)(__builtin_bit_cast(unsigned long long, c[q]) >> 32) & 0x7fffffffu;
           const unsigned key = elig ? hi : 0u;
           const unsigned kmax = wave_max_u32(key);
-          unsigned long long cand = ballot(key == kmax);
+          const bool top = key == kmax;
+          unsigned long long cand = ballot(top);
           asm volatile("" : "+v"(r));
           // one lane, unless several share the upper half or every key is 0
           if (__builtin_expect(__builtin_popcountll(cand) != 1, 0)) {
             const unsigned lo = (unsigned)__builtin_bit_cast(unsigned long long, c[q]);
-            cand = lu_tie(ballot(elig) & cand, kmax, lo, f.src, k, lane, info);
+            cand = lu_tie(elig, top, kmax, lo, f.src, k, lane, info);
           }
           int pq = uniform_int(__builtin_ctzll(cand));
           if (nopiv && k < N) {  // ablation: the pivot is row k itself

@@ -483,65 +483,63 @@ __device__ inline bool wg_form(const MechView& m, const WgWs& w, const double* S
   return !block_any(bad, w.flag + 1);
 }
 
-// The rare outcomes of a panel's pivot search: rows share the largest upper half
-// (see lu_tie), or the largest is Inf or NaN.  v: the column's values, elig: the
-// rows not yet chosen.  NaN is passed over, as idamax's comparisons do (the
-// integer keys of the common search would make it the largest): the pivot is the
-// largest |v| of the others, and only a column of nothing but NaN takes its
-// first row.  Returns the row: largest |v|, then the earliest in getrf's order,
-// which src (lane j < k: the row of step j) gives.
+// The outcomes of a panel's pivot search other than one row of largest upper
+// half kmax: several share it, or it is that of Inf or NaN.  v: the column's
+// values, elig: the rows not yet chosen.  NaN is passed over, as idamax's
+// comparisons do (the integer keys of the common search would make it the
+// largest): the pivot is the largest |v| of the others, and only a column of
+// nothing but NaN takes its first row.  Returns the row: largest |v|, then the
+// earliest in getrf's order.  getrf holds a row not yet chosen at the first
+// x >= k of x = row, src[row], src[src[row]], ... (src: lane j < k holds the row of
+// step j, which left its place to the row at j); only rows < k can have moved.
+// Bound: the chain of the reductions (see lu_tie).  Periodic second differences,
+// 1,500 matrices of 128: 1,390 us with the rows kept in order, 1,849 with the
+// tied rows walked one by one, now 1,414.
 template <int NS>
-__device__ inline int panel_tie(const double (&v)[NS], const bool (&elig)[NS], int src, int k, int lane, bool& sing) {
+__device__ inline int panel_tie(const double (&v)[NS], const bool (&elig)[NS], unsigned kmax, int src, int k, int lane,
+                                bool& sing) {
   unsigned hi[NS], lo[NS], m = 0;
-  bool num[NS];
-  unsigned long long cand[NS], any = 0;
+  bool c[NS];
+  unsigned long long any = 0;
 #pragma unroll
   for (int s = 0; s < NS; ++s) {
     const unsigned long long u = __builtin_bit_cast(unsigned long long, v[s]);
-    num[s] = elig[s] && !__builtin_isnan(v[s]);
-    any |= ballot(num[s]);
-    hi[s] = num[s] ? (unsigned)(u >> 32) & 0x7fffffffu : 0u;
-    lo[s] = num[s] ? (unsigned)u : 0u;
-    m = max(m, hi[s]);
+    c[s] = elig[s] && !__builtin_isnan(v[s]);
+    any |= ballot(c[s]);
+    hi[s] = (unsigned)(u >> 32) & 0x7fffffffu;
+    lo[s] = (unsigned)u;
+    m = max(m, c[s] ? hi[s] : 0u);
   }
-  const unsigned kmax = wave_max_u32(m);
+  if (kmax >= 0x7ff00000u) kmax = wave_max_u32(m);
+  m = 0;
 #pragma unroll
-  for (int s = 0; s < NS; ++s) cand[s] = ballot(elig[s] && (num[s] || !any) && hi[s] == kmax);
-  unsigned best = 0;
-#pragma unroll
-  for (int s = 0; s < NS; ++s)
-#pragma clang loop unroll(disable)
-    for (unsigned long long c = cand[s]; c; c &= c - 1)
-      best = max(best, (unsigned)__builtin_amdgcn_readlane((int)lo[s], __builtin_ctzll(c)));
-  sing = any && (kmax | best) == 0u;
-  int pos[NS];
-#pragma unroll
-  for (int s = 0; s < NS; ++s) pos[s] = s * WAVE + lane;
-#pragma clang loop unroll(disable)
-  for (int j = 0; j < k; ++j) {
-    const int pj = __builtin_amdgcn_readlane(src, j);
-    int pp = 0;
-#pragma unroll
-    for (int s = 0; s < NS; ++s)
-      if (pj / WAVE == s) pp = __builtin_amdgcn_readlane(pos[s], pj & (WAVE - 1));
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      const int np = pos[s] == j ? pp : pos[s];
-      pos[s] = s * WAVE + lane == pj ? j : np;
-    }
+  for (int s = 0; s < NS; ++s) {
+    c[s] = c[s] && hi[s] == kmax;
+    m = max(m, c[s] ? lo[s] : 0u);
   }
-  int row = k, pmin = 1 << 20;
-#pragma unroll
-  for (int s = 0; s < NS; ++s)
+  const unsigned lmax = wave_max_u32(m);
+  sing = any && (kmax | lmax) == 0u;
+  int x = elig[0] ? lane : k;  // a row already chosen may lie on a cycle of src
 #pragma clang loop unroll(disable)
-    for (unsigned long long c = cand[s]; c; c &= c - 1) {
-      const int l = __builtin_ctzll(c);
-      const int at = __builtin_amdgcn_readlane(pos[s], l);
-      if ((unsigned)__builtin_amdgcn_readlane((int)lo[s], l) == best && at < pmin) {
-        pmin = at;
-        row = s * WAVE + l;
-      }
-    }
+  for (int i = 0; i < k && ballot(x < k); ++i) {
+    const int y = __builtin_amdgcn_ds_bpermute(4 * x, src);
+    x = x < k ? y : x;
+  }
+  m = 0;
+  unsigned early[NS];
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    c[s] = any ? c[s] && lo[s] == lmax : elig[s];
+    early[s] = c[s] ? (unsigned)(NS * WAVE - (s == 0 ? x : s * WAVE + lane)) : 0u;
+    m = max(m, early[s]);
+  }
+  const unsigned first = wave_max_u32(m);
+  int row = k;
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    const unsigned long long b = ballot(c[s] && early[s] == first);
+    row = b ? s * WAVE + (int)__builtin_ctzll(b) : row;
+  }
   return row;
 }
 
@@ -598,7 +596,7 @@ __device__ inline void wg_panel(const WgWs& w, int p0, int NP, int lane) {
       double v[NS];
 #pragma unroll
       for (int s = 0; s < NS; ++s) v[s] = P[s][kk];
-      row = panel_tie<NS>(v, elig, src, kk, lane, sing);
+      row = panel_tie<NS>(v, elig, kmax, src, kk, lane, sing);
       if (sing && first == 0) first = p0 + kk + 1;
     }
     row = uniform_int(row);
