@@ -133,22 +133,24 @@ __global__ void k_reset(int* q, unsigned long long* failed) {
   }
 }
 
-// f (and J, if given) of every cell, one cell per wave.  WALK: the grid fills
-// the chip once and walks the cells, so a workgroup stages its tables once.  J
+// f (and J: JAC) of every cell, one cell per wave.  WALK: the grid fills the
+// chip once and walks the cells, so a workgroup stages its tables once.  J
 // leaves LDS in address order: with a row per lane each store of a wave touched
 // 55 lines 440 bytes apart.
-// Bound: the waves that fit (jac_pass is a chain through LDS; J's block limits a
-// CU to four), the 726 MB of J of 30,000 cells of 54 species take 160 us at the
-// rate of a copy.  One row per lane, tables staged for every four cells: 909
-// us; now 712.  f alone keeps no J block, so twice the waves fit: 60,000 cells
-// 486 -> 252 us.
-template <int NP, bool WALK>
+// Bound: the waves that fit (both passes are chains through LDS).  J's block
+// limits a CU to four at 54 species; the 726 MB of J of 30,000 cells take 160 us
+// at the rate of a copy.  One row per lane, tables staged for every four cells:
+// 909 us; now 710.  f has a kernel of its own: no Jacobian block in LDS and 58
+// registers, where one kernel for both took 121 (173 walking).  60,000 cells of
+// 53 species 505 -> 213 us, of 16 114 -> 104 (142 while f shared the walking
+// kernel).
+template <int NP, bool JAC, bool WALK>
 __global__ __launch_bounds__(max_threads<NP>()) void k_rhs_jac(IntArgs a, const double* st, double* f, double* J) {
   extern __shared__ __align__(16) uint8_t lds[];
   stage_blob(lds, a.blob, a.d.lds_bytes);
   const MechView m = make_view(lds, a);
   const int wv = threadIdx.x / WAVE, wpb = blockDim.x / WAVE;
-  const CellWs w = make_ws((double*)(lds + a.d.lds_bytes) + (size_t)wv * a.cell_doubles, a.d, J != nullptr);
+  const CellWs w = make_ws((double*)(lds + a.d.lds_bytes) + (size_t)wv * a.cell_doubles, a.d, JAC);
   const int lane = lane_id();
   const int N = m.d.N, S = m.d.S;
   if (lane == 0) {
@@ -161,13 +163,30 @@ __global__ __launch_bounds__(max_threads<NP>()) void k_rhs_jac(IntArgs a, const 
   for (int64_t c = (int64_t)blockIdx.x * wpb + wv; c < a.ncells; c += (int64_t)gridDim.x * wpb) {
     const double y = lane < N ? st[(int64_t)lane * a.ld + c] : 0.0;
     double fv;
-    if (J) {
+    if constexpr (JAC) {
       fv = jac_pass<NP>(m, w, y, a.p, lane);
-      const int rows = WAVE / N, r0 = lane / N, col = lane - r0 * N;  // rows per store, the lane's row and column
       double* Jc = J + (size_t)c * N * N;
-      if (r0 < rows) {
-#pragma clang loop unroll_count(4)
-        for (int i = r0; i < N; i += rows) Jc[i * N + col] = w.J[i * S + col];
+      if constexpr (NP > 32) {  // one row a store; LDS offsets of a step are constants
+        const double* Jl = w.J + lane;
+        if (lane < N) {
+          int i = 0;
+#pragma clang loop unroll(disable)
+          for (; i + 8 <= N; i += 8) {
+            double v[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] = Jl[(i + q) * (NP + 1)];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) Jc[(i + q) * N + lane] = v[q];
+          }
+#pragma clang loop unroll(disable)
+          for (; i < N; ++i) Jc[i * N + lane] = Jl[i * (NP + 1)];
+        }
+      } else {
+        const int rows = WAVE / N, r0 = lane / N, col = lane - r0 * N;  // rows per store, the lane's row and column
+        if (r0 < rows) {
+#pragma clang loop unroll_count(8)
+          for (int i = r0; i < N; i += rows) Jc[i * N + col] = w.J[i * S + col];
+        }
       }
     } else {
       fv = rhs(m, w, y, a.p, lane);
@@ -566,6 +585,7 @@ struct chem_mech {
   int32_t* adj_tptr = nullptr;
   uint32_t* jsched = nullptr;  // balanced species-scatter schedule of the Jacobian (wavefront path)
   int jsched_it = 0;
+  int64_t jac_fill = 0;        // see jac_walk_fill (wavefront path)
   uint32_t* adj_tent = nullptr;
   uint32_t* adj_chunk = nullptr;  // wavefront path: the sent lists cut into <= 64 chunks, [cw][64]
   int32_t* adj_cspan = nullptr;   // [K] first chunk | count << 8
@@ -599,6 +619,8 @@ int max_wpb(const chem_mech* m) {
   return std::min(w, np_for(m->d.N) <= 16 ? MAX_WPB : 4);
 }
 
+int rhs_jac_wpb(const chem_mech* m) { return std::max(1, std::min(4, max_wpb(m))); }
+
 IntArgs base_args(const chem_mech* m) {
   IntArgs a{};
   a.blob = m->blob;
@@ -625,6 +647,32 @@ template <int NP>
 int set_lds_limit(const void* fn, size_t bytes) {
   HIPCHK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
   return 0;
+}
+
+// Workgroups of k_rhs_jac beyond which the grid walks the cells to J (one fill
+// of the chip), or none.  The loop costs registers (115 -> 175: eight waves a CU
+// instead of sixteen), so it walks only where LDS lets no more workgroups in
+// anyway: from about 30 species (J of 20,000 cells of 31: 170 us, walking 172; of
+// 53: 505 and 466).  Below, walking loses: of 16, 81 and 111; of 24, 119 and 147.
+// f never walks: of 60,000 cells of 31 species 119 us, walking 131; of 53, 213
+// and 210.  Asked once per mechanism: the two queries are 0.5 us, which a call of
+// a few cells would notice.
+int64_t jac_walk_fill(const chem_mech* m) {
+  int walk = 0, plain = 0;
+  const int wpb = rhs_jac_wpb(m);
+  const size_t lds = m->d.lds_bytes + (size_t)wpb * cell_bytes(m->d);
+  with_np(m->d.N, [&](auto npc) -> int {
+    constexpr int NP = decltype(npc)::value;
+    if constexpr (NP > 16) {
+      if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&walk, k_rhs_jac<NP, true, true>, wpb * WAVE, lds) != hipSuccess ||
+          hipOccupancyMaxActiveBlocksPerMultiprocessor(&plain, k_rhs_jac<NP, true, false>, wpb * WAVE, lds) != hipSuccess) {
+        walk = 0;
+        (void)hipGetLastError();
+      }
+    }
+    return 0;
+  });
+  return walk > 0 && walk >= plain ? (int64_t)m->ncu * walk : INT64_MAX;
 }
 
 // LDS of the workgroup-path kernels (workspace only: they read the
@@ -794,31 +842,22 @@ int launch_integrate(chem_mech* m, const IntArgs& a0, const Variant& v, hipStrea
   });
 }
 
-// f (and J unless null) of every cell.  Without J a wave needs no Jacobian block.
+// f (and J: JAC) of every cell.  Without J a wave needs no Jacobian block.
+template <bool JAC>
 int launch_rhs_jac(const chem_mech* m, const IntArgs& a0, const double* state, double* f, double* J, hipStream_t s) {
   if (m->wg) return launch_rhs_jac_wg(const_cast<chem_mech*>(m), a0, state, f, J, s);
   IntArgs a = a0;
-  if (!J) a.cell_doubles = wave_rates_doubles(m->d.R, m->d.R0);
-  const int wpb = std::max(1, std::min(4, max_wpb(m)));
+  if (!JAC) a.cell_doubles = wave_rates_doubles(m->d.R, m->d.R0);
+  const int wpb = rhs_jac_wpb(m);
   const size_t lds = m->d.lds_bytes + (size_t)wpb * a.cell_doubles * sizeof(double);
   return with_np(m->d.N, [&](auto npc) -> int {
     constexpr int NP = decltype(npc)::value;
-    const int64_t need = (a.ncells + wpb - 1) / wpb;
-    int64_t grid = need;
-    auto kern = k_rhs_jac<NP, false>;
-    // Walk where the cells exceed one fill of the chip: the tables are staged
-    // once instead of once per four cells.  The loop costs registers (121 ->
-    // 173), so calls that fit keep one cell per wave (f of 1,000 cells of 54
-    // species: 10.5 us, walking 11.2), and so do up to 15 species, whose tables
-    // are small and whose waves the registers limit (f of 60,000 cells of 10:
-    // 80 us, walking 100; their J of 16,000: 45 and 60).
-    if constexpr (NP > 16) {
-      int occ = 0;
-      HIPCHK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_rhs_jac<NP, true>, wpb * WAVE, lds));
-      const int64_t fill = (int64_t)m->ncu * std::max(occ, 1);
-      if (need > fill) {
-        grid = fill;
-        kern = k_rhs_jac<NP, true>;
+    int64_t grid = (a.ncells + wpb - 1) / wpb;
+    auto kern = k_rhs_jac<NP, JAC, false>;
+    if constexpr (JAC && NP > 16) {
+      if (grid > m->jac_fill) {
+        grid = m->jac_fill;
+        kern = k_rhs_jac<NP, true, true>;
       }
     }
     if (set_lds_limit<NP>((const void*)kern, lds)) return CHEM_EHIP;
@@ -1269,6 +1308,7 @@ int chem_load_mechanism(const chem_mech_desc* desc, chem_mech** out) {
     return cleanup(CHEM_EHIP, "upload failed");
   // the failed-cell counter shares the 64-byte queue allocation (the cursor is its first word)
   m->failed = reinterpret_cast<unsigned long long*>(reinterpret_cast<uint8_t*>(m->queue) + 8);
+  if (!wg) m->jac_fill = jac_walk_fill(m);
   *out = m;
   return CHEM_OK;
 }
@@ -1557,7 +1597,7 @@ int chem_rhs(const chem_mech* m, int64_t ncells, int64_t ld, const double* state
   a.ld = ld;
   a.ncells = ncells;
   a.p = 10.0 * p;
-  return launch_rhs_jac(m, a, state, f, nullptr, (hipStream_t)stream);
+  return launch_rhs_jac<false>(m, a, state, f, nullptr, (hipStream_t)stream);
 }
 
 int chem_jacobian(const chem_mech* m, int64_t ncells, int64_t ld, const double* state, double p, double* J,
@@ -1569,7 +1609,7 @@ int chem_jacobian(const chem_mech* m, int64_t ncells, int64_t ld, const double* 
   a.ld = ld;
   a.ncells = ncells;
   a.p = 10.0 * p;
-  return launch_rhs_jac(m, a, state, f, J, (hipStream_t)stream);
+  return launch_rhs_jac<true>(m, a, state, f, J, (hipStream_t)stream);
 }
 
 // Workgroup LU (64 < n <= 256): one matrix per 256-thread workgroup, an
