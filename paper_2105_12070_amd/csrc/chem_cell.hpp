@@ -733,12 +733,19 @@ __device__ __forceinline__ int lu_factor(MatTiles<NP>& M, double (&row)[NP], int
         block_transpose(nl);  // -> operand B of row tile t, lane i: -L[16 t + i % 16][k0 + i / 16]
         // The lane swaps write both operands, and the compiler (ROCm 7.2) does not
         // keep the wait states that an MFMA reading the second one needs: one
-        // instruction after the swap it read the old value.  The eight values pass
-        // through the wait, so neither swaps nor MFMAs can move across it.  Its
-        // length (4) is a margin over that observation, not a documented figure.
+        // instruction after the swap it read the old value.  Every MFMA takes its
+        // nl from the wait, and its u was taken up before it (volatile statements
+        // keep their order), so neither swaps nor MFMAs can move across.  The
+        // wait's length (4) is a margin over that observation, not a documented
+        // figure.
         __builtin_amdgcn_sched_barrier(0);
-        asm volatile("s_nop 3"
-                     : "+v"(u[0]), "+v"(u[1]), "+v"(u[2]), "+v"(u[3]), "+v"(nl[0]), "+v"(nl[1]), "+v"(nl[2]), "+v"(nl[3]));
+        static_for<tc, NT>([&](auto Cc) __attribute__((always_inline)) {
+          double& uc = u[decltype(Cc)::value];
+          asm volatile("" : "+v"(uc));
+        });
+        if constexpr (NT == 1) asm volatile("s_nop 3" : "+v"(nl[0]));
+        else if constexpr (NT == 2) asm volatile("s_nop 3" : "+v"(nl[0]), "+v"(nl[1]));
+        else asm volatile("s_nop 3" : "+v"(nl[0]), "+v"(nl[1]), "+v"(nl[2]), "+v"(nl[3]));
         __builtin_amdgcn_sched_barrier(0);
         static_for<0, NT>([&](auto Tc) __attribute__((always_inline)) {
           constexpr int t = decltype(Tc)::value;

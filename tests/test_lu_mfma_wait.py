@@ -46,14 +46,28 @@ def code(tmp_path_factory):
 
 
 def test_operands_pass_through_the_wait(code):
+    """The multipliers come out of the wait, the rows of U out of a statement that stands before it in the same block
+    (volatile statements keep their order)."""
     count = 0
     for fn in re.findall(r"^define .*?^}", code[1], re.M | re.S):
-        defs = dict(re.findall(r"^\s*(%\S+) = (.*)$", fn, re.M))
+        defs = {}
+        for line, text in enumerate(fn.splitlines()):
+            m = re.match(r"\s*(%\S+) = (.*)$", text)
+            if m:
+                defs[m.group(1)] = (line, m.group(2))
+
+        def source(v):
+            line, d = defs[v]
+            m = re.match(r"extractvalue \{.*\} (%\S+), \d", d)
+            return defs[m.group(1)] if m else (line, d)
+
         for a, b in re.findall(r"@llvm\.amdgcn\.mfma\.f64\.16x16x4f64\(double (%\S+), double (%\S+),", fn):
             count += 1
-            for v in (a, b):
-                d = re.match(r"extractvalue \{.*\} (%\S+), \d", defs[v])
-                assert d and 'asm sideeffect "s_nop' in defs[d.group(1)], defs[v]
+            (la, da), (lb, db) = source(a), source(b)
+            assert 'asm sideeffect ""' in da, da
+            assert 'asm sideeffect "s_nop' in db, db
+            between = fn.splitlines()[la:lb]
+            assert la < lb and not any(t.startswith(("br ", "  br ")) or re.match(r"\S+:", t) for t in between)
     assert count > 50
 
 
