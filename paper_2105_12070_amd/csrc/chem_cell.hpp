@@ -588,9 +588,9 @@ struct MatTiles {
 // the tile's registers rotate by one column group per panel, so the current
 // group is always the first (unrolled over all panels the code, 110 KB for the
 // integrator, no longer fits the instruction cache).
-// Measured for N = 55 (shader cycles of one factorisation, two waves per SIMD /
-// one wave): 87.9k / 67.5k row-per-lane with the rows permuted at the end, 54.7k /
-// 42.3k this way (a solve with the factors 5.7k / 5.2k -> 2.9k / 2.2k).
+// Measured for N = 55 in a loop of its own (shader cycles of one factorisation,
+// two waves per SIMD / one wave): 87.9k / 67.5k row-per-lane with the rows permuted
+// at the end, 54.7k / 42.3k this way.
 // FACTORS: the factors are the result, and a NaN stays in the rows and columns
 // that the elimination takes it to.  A solve needs no such care (a NaN
 // multiplier makes every x NaN), and the integrators have no register for it

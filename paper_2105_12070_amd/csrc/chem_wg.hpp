@@ -553,8 +553,9 @@ __device__ inline int panel_tie(const double (&v)[NS], const bool (&elig)[NS], u
 // Records piv, 1/U_kk and the first zero pivot in flag[2].
 // Bound: the serial chain of wave 0 (the other waves wait).  With physical row
 // swaps, three dependent searches and the reciprocal after them a column took
-// 1,510 cycles (241k of an attempt at 151 species, two workgroups a CU); now
-// 950 (152k).
+// 1,510 cycles (241k of an attempt at 150 species, two workgroups a CU); now
+// 1,040 (166k), 80 of them for leaving the rows already chosen out of the update
+// instead of multiplying them by 0.
 template <int NS>
 __device__ inline void wg_panel(const WgWs& w, int p0, int NP, int lane) {
   const int nrow = NP - p0;
